@@ -37,7 +37,7 @@ BYTES_PER_FIELD = {0: 4, 1: 2, 2: 2}
 
 # the sources the tiled update kernel is compiled from: HBM counters taken
 # with other sources are not reported as this kernel's traffic
-KERNEL_SOURCES = ("update_tiled.hip", "tslb_tiles.h", "tslb_device.h", "tslb_params.h")
+KERNEL_SOURCES = ("update_tiled_kernel.h", "update_tiled.hip", "tslb_tiles.h", "tslb_device.h", "tslb_params.h")
 
 
 def _source_hash():

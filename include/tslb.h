@@ -173,7 +173,7 @@ int tslb_step(tslb_handle h, int nsteps, void *stream);
 /* tslb_step with per-launch timing, for profiling: HIP events recorded on
  * `stream` around every launch give ms[0] = summed device time of the main
  * update kernel launches and ms[1] = summed time of the per-step auxiliary
- * launches (wall fix-up, ghost refill).  Synchronises the stream.  The
+ * launches (the ghost refill).  Synchronises the stream.  The
  * events add a few microseconds between launches, so tslb_step is the one to
  * time whole runs with.  1 <= nsteps <= 100000.                             */
 int tslb_step_timed(tslb_handle h, int nsteps, double ms[2], void *stream);

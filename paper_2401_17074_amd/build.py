@@ -5,7 +5,8 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["capi.hip", "aux_kernels.hip", "update_direct.hip", "update_tiled.hip", "adjoint_tiled.hip",
+SOURCES = ["capi.hip", "aux_kernels.hip", "update_direct.hip", "update_tiled.hip", "update_tiled_f32.hip",
+           "update_tiled_f16.hip", "update_tiled_bf16.hip", "adjoint_tiled.hip",
            "update_poplayout.hip", "stats.hip",
            "update_d2q9.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Wall",
@@ -15,7 +16,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Wall",
 
 def build(verbose=False, defines=()):
     """Compile and link libtslb.so (all sources in parallel).  `defines`
-    (e.g. ("TSLB_NT_STORE=0", "TSLB_WAVES_PER_EU=3")) are build-time tuning
+    (e.g. ("TSLB_TILE_Y=11", "TSLB_WAVES_PER_EU=3")) are build-time tuning
     overrides of the tiled kernels."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     obj_dir = os.path.join(ROOT, "_build")

@@ -39,8 +39,7 @@ inline hipStream_t S(void* s) { return (hipStream_t)s; }
 
 inline bool ghost_kind(int k) { return k == TSLB_INLET || k == TSLB_OUTLET; }
 
-// The update proper (without the wall fix-up pass of the tiled kernel).
-hipError_t run_main_update(tslb_ctx* h, const void* in, void* out, hipStream_t s) {
+hipError_t run_update(tslb_ctx* h, const void* in, void* out, hipStream_t s) {
     if (h->lattice == TSLB_D2Q9) return launch_update_d2q9(h->storage, in, out, h->p, s);
     switch (h->kernel) {
     case 0: return launch_update_tiled(h->storage, in, out, h->p, s);
@@ -48,12 +47,6 @@ hipError_t run_main_update(tslb_ctx* h, const void* in, void* out, hipStream_t s
     case 2: return launch_update_poplayout(h->storage, in, out, h->pop, h->p, s);
     }
     return hipErrorInvalidValue;
-}
-
-hipError_t run_update(tslb_ctx* h, const void* in, void* out, hipStream_t s) {
-    hipError_t e = run_main_update(h, in, out, s);
-    if (e != hipSuccess || h->kernel != 0 || h->lattice == TSLB_D2Q9) return e;
-    return launch_wall_fixup(h->storage, in, out, h->p, s);
 }
 
 // Make `dev` current for the duration of a call.
@@ -75,7 +68,7 @@ int ensure_staging(tslb_ctx* h) {
     return TSLB_OK;
 }
 
-// after_update: st was just written by run_update / run_main_update, so the
+// after_update: st was just written by run_update, so the
 // tiled D3 update may already have refilled the plain x-face ghost nodes
 int fill_ghosts(tslb_ctx* h, void* st, hipStream_t s, bool after_update = false) {
     if (!h->has_ghosts) return TSLB_OK;
@@ -186,15 +179,6 @@ int tslb_create(int nx, int ny, int nz, int lattice, float tau, const float forc
     h->inlet.seed = b.seed;
     h->inlet.noise_kind = b.inlet_noise_kind;
     h->has_ghosts = (g.lo_ghost | g.hi_ghost) != 0;
-    // layers next to wall faces (raw sums of the tiled update, fix-up pass)
-    h->p.wall_nodes = 0;
-    for (int f = 0; f < 6; ++f) {
-        const int d = f >> 1, d1 = d == 0 ? 1 : 0, d2 = d == 2 ? 1 : 2;
-        const bool wall = (f & 1) ? ((g.hi_solid >> d) & 1) : ((g.lo_solid >> d) & 1);
-        h->p.wall_off[f] = wall ? h->p.wall_nodes : -1;
-        if (wall) h->p.wall_nodes += (long long)dims[d1] * dims[d2];
-    }
-    h->p.wall_side = nullptr;
     h->storage = b.storage;
     h->elem_bytes = b.storage == TSLB_FP32 ? 4 : 2;
     h->kernel = 0;
@@ -202,9 +186,7 @@ int tslb_create(int nx, int ny, int nz, int lattice, float tau, const float forc
     const size_t bytes = h->elem_bytes * 10 * (size_t)g.N;
     if (hipMalloc(&h->buf[0], bytes) != hipSuccess || hipMalloc(&h->buf[1], bytes) != hipSuccess ||
         hipMalloc((void**)&h->red_partials, sizeof(double) * kRedSums * h->red_blocks) != hipSuccess ||
-        hipMalloc((void**)&h->red_out, sizeof(double) * kRedSums) != hipSuccess ||
-        (h->p.wall_nodes > 0 && tiled_uses_wall_side() &&
-         hipMalloc((void**)&h->p.wall_side, sizeof(float) * 10 * (size_t)h->p.wall_nodes) != hipSuccess)) {
+        hipMalloc((void**)&h->red_out, sizeof(double) * kRedSums) != hipSuccess) {
         tslb_destroy(h);
         return fail(TSLB_E_NOMEM, "device allocation of 2 x %zu bytes failed", bytes);
     }
@@ -250,7 +232,6 @@ int tslb_destroy(tslb_handle h) {
     (void)hipFree(h->staging);
     (void)hipFree(h->red_partials);
     (void)hipFree(h->red_out);
-    (void)hipFree(h->p.wall_side);
     (void)hipFree(h->pop);
     (void)hipFree(h->omo_z);
     (void)hipFree(h->stats_prof);
@@ -517,10 +498,8 @@ int tslb_step_timed(tslb_handle h, int nsteps, double ms[2], void* stream) {
         void* in = h->buf[h->cur];
         void* out = h->buf[1 - h->cur];
         hipError_t e = hipEventRecord(ev[3 * k], s);
-        if (e == hipSuccess) e = run_main_update(h, in, out, s);
+        if (e == hipSuccess) e = run_update(h, in, out, s);
         if (e == hipSuccess) e = hipEventRecord(ev[3 * k + 1], s);
-        if (e == hipSuccess && h->kernel == 0 && h->lattice != TSLB_D2Q9)
-            e = launch_wall_fixup(h->storage, in, out, h->p, s);
         if (e != hipSuccess) {
             rc = fail(TSLB_E_HIP, "timed step: %s", hipGetErrorString(e));
             break;

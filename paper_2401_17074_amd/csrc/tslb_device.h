@@ -62,27 +62,6 @@ __device__ __forceinline__ bool is_fluid(const Geometry& g, int x, int y, int z)
     return f;
 }
 
-// Wall face next to a fluid node (the first of -x, +x, -y, +y, -z, +z whose
-// wall layer is a neighbour), or -1.  Faces: bit d of lo_solid / hi_solid.
-__device__ __forceinline__ int first_wall_face(const Geometry& g, const int c[3]) {
-#pragma unroll
-    for (int f = 0; f < 6; ++f) {
-        const int d = f >> 1;
-        const bool wall = (f & 1) ? ((g.hi_solid >> d) & 1) : ((g.lo_solid >> d) & 1);
-        const int layer = (f & 1) ? g.n[d] - 2 : 1;
-        if (wall && c[d] == layer) return f;
-    }
-    return -1;
-}
-
-// Position of a node inside the layer of face f: the two transverse
-// coordinates (in x, y, z order) as a + n_a * b.
-__device__ __forceinline__ long long wall_layer_index(const Geometry& g, int f, const int c[3]) {
-    const int d = f >> 1;
-    const int d1 = d == 0 ? 1 : 0, d2 = d == 2 ? 1 : 2;
-    return (long long)c[d1] + (long long)g.n[d1] * c[d2];
-}
-
 // ------------------------------------------------------------------ storage
 // Stored field q of a node: FP32 as is; FP16 / BF16 hold value * scale[q]
 // rounded to nearest even.  Field 0 holds rho - 1.
@@ -235,28 +214,25 @@ __device__ __forceinline__ void finalize(const MomentSums& a, float out[10]) {
     out[9] = (a.s[5] - a.j[1] * uz) * kInv;
 }
 
-// finalize() with the stored fields' scales s0 (drho), s1 (u), s2 (Pi)
-// applied: folded into the 1/SCALE factor where there is one (the same
-// values, since the scales are powers of two).
+// finalize() without the factor 1 / SCALE of drho and Pi', which 16-bit
+// storage applies together with the stored field's scale as it rounds.
 template <int SCALE = 216>
-__device__ __forceinline__ void finalize_scaled(const MomentSums& a, float s0, float s1, float s2, float out[10]) {
-    constexpr float kInv = 1.0f / (float)SCALE;
-    const float k0 = kInv * s0, k2 = kInv * s2;
+__device__ __forceinline__ void finalize_unscaled(const MomentSums& a, float out[10]) {
     const float den = (float)SCALE + a.d;
     float inv = __builtin_amdgcn_rcpf(den);
     inv = inv * fmaf(-den, inv, 2.0f);
     const float ux = a.j[0] * inv, uy = a.j[1] * inv, uz = a.j[2] * inv;
     const float d3 = a.d * (1.0f / 3.0f);
-    out[0] = a.d * k0;
-    out[1] = ux * s1;
-    out[2] = uy * s1;
-    out[3] = uz * s1;
-    out[4] = (a.s[0] - a.j[0] * ux - d3) * k2;
-    out[5] = (a.s[1] - a.j[1] * uy - d3) * k2;
-    out[6] = (a.s[2] - a.j[2] * uz - d3) * k2;
-    out[7] = (a.s[3] - a.j[0] * uy) * k2;
-    out[8] = (a.s[4] - a.j[0] * uz) * k2;
-    out[9] = (a.s[5] - a.j[1] * uz) * k2;
+    out[0] = a.d;
+    out[1] = ux;
+    out[2] = uy;
+    out[3] = uz;
+    out[4] = a.s[0] - a.j[0] * ux - d3;
+    out[5] = a.s[1] - a.j[1] * uy - d3;
+    out[6] = a.s[2] - a.j[2] * uz - d3;
+    out[7] = a.s[3] - a.j[0] * uy;
+    out[8] = a.s[4] - a.j[0] * uz;
+    out[9] = a.s[5] - a.j[1] * uz;
 }
 
 // Compile-time loop over the 27 velocities.

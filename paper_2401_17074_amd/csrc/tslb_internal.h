@@ -20,7 +20,6 @@ hipError_t launch_update_poplayout(int storage, const void* in, void* out, float
 hipError_t tiled_schedule(const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg);
 hipError_t launch_update_tiled(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
 hipError_t launch_update_d2q9(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
-bool tiled_uses_wall_side();  // the tiled update needs the wall side buffer and the fix-up launch
 int stats_blocks_per_plane(const Geometry& g, int axis);
 int stats_jet_bins(const Geometry& g, int axis, float c1, float c2);
 hipError_t launch_stats_profile(int storage, const void* st, double* part, double* sums, const StepParams& p,
@@ -30,8 +29,6 @@ hipError_t launch_stats_field_moments(const double* fs, long long N, double inv_
                                       hipStream_t s);
 hipError_t launch_stats_jet(const double* fs, const Geometry& g, int axis, float c1, float c2, double inv_ns,
                             float* uc, float* rhalf, hipStream_t s);
-// Completes the wall-adjacent nodes after launch_update_tiled (walls only).
-hipError_t launch_wall_fixup(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
 // x_done: the tiled update has written the ghost nodes of the x faces that
 // lie on no other ghost face (inlet velocities are still imposed here)
 hipError_t launch_ghost_fill(int storage, void* st, const StepParams& p, const InletParams& q, int64_t t,

@@ -20,14 +20,6 @@ struct StepParams {
     const float* gfield;     // optional per-node acceleration, 3N SoA
     float scale[3];          // storage scales (drho, u, Pi); 1 for FP32
     float inv_scale[3];
-    // Wall-adjacent fluid nodes when the tiled update is built without the
-    // in-kernel bounce-back (TSLB_FUSED_WALLS=0): it leaves their raw moment
-    // sums here (FP32, ten per node) and a fix-up launch adds the
-    // bounced-back populations.  The layer next to wall face f starts at
-    // wall_off[f] nodes (-1: face f is not a wall).
-    float* wall_side;
-    long long wall_off[6];
-    long long wall_nodes;
     // Work list of the tiled update (see tile::Schedule): sched_grid blocks,
     // sched_nseg entries {tile column, z begin, z end, 0} per block.
     const int4* sched;

@@ -5,6 +5,7 @@
 // marched z-extent.
 #pragma once
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "tslb_internal.h"
@@ -18,17 +19,8 @@ namespace tile {
 #ifndef TSLB_TILE_Y
 #define TSLB_TILE_Y 12
 #endif
-#ifndef TSLB_NT_STORE
-#define TSLB_NT_STORE 1
-#endif
 #ifndef TSLB_WAVES_PER_EU
 #define TSLB_WAVES_PER_EU 4
-#endif
-// 1 (default): the tiled update adds the bounced-back populations of
-// wall-adjacent nodes itself, from the populations the node has just built;
-// 0: it leaves their raw sums in a side buffer for the wall fix-up launch
-#ifndef TSLB_FUSED_WALLS
-#define TSLB_FUSED_WALLS 1
 #endif
 constexpr int TX = TSLB_TILE_X;              // interior tile width (64: one wave per row)
 constexpr int TY = TSLB_TILE_Y;              // interior rows
@@ -165,6 +157,12 @@ __host__ __device__ constexpr float scaled_weight(int n0) {
     return (float)(1 << (2 * n0));
 }
 
+// Does velocity I carry a population (D3Q19 has no corners)?
+template <int LAT>
+__host__ __device__ constexpr bool carries(int I) {
+    return scaled_weight<LAT>((cx_of(I) == 0) + (cy_of(I) == 0) + (cz_of(I) == 0)) != 0.0f;
+}
+
 // Values of the 2D polynomial Q(cx, cy) = sum b_ab cx^a cy^b on the 3 x 3
 // velocity grid of one cz slice, written to G[base + 3 (cy + 1) + (cx + 1)]
 // with the exact scaled weight applied (WEIGHTED), or without it for a
@@ -260,75 +258,14 @@ __device__ __forceinline__ void add_slice(const float F[3][3], MomentSums& a) {
 // other row lengths a wave's row straddles lines that the neighbouring tile
 // completes, and plain stores let L2 merge the two halves before they go to
 // memory (the launch decides, NT).
-template <bool NT, class T>
-__device__ __forceinline__ void store_out(T* p, T v) {
-    if constexpr (NT && TSLB_NT_STORE) {
-        if constexpr (sizeof(T) == 4)
-            __builtin_nontemporal_store(__builtin_bit_cast(float, v), reinterpret_cast<float*>(p));
-        else
-            __builtin_nontemporal_store(__builtin_bit_cast(unsigned short, v), reinterpret_cast<unsigned short*>(p));
-    } else {
+template <class T>
+using store_bits = std::conditional_t<sizeof(T) == 4, unsigned, unsigned short>;
+template <bool NT, class P, class T>
+__device__ __forceinline__ void store_out(P p, T v) {
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, p);
+    else
         *p = v;
-    }
-}
-
-// Field q of node n: a uniform per-field base plus a 32-bit node offset, so
-// the address is one scalar base and one shared vector offset (the grid
-// holds fewer than 2^30 nodes, checked at launch).
-template <class T>
-__device__ __forceinline__ T ld_at(const T* __restrict__ base, unsigned byte_off) {
-    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + byte_off);
-}
-
-template <class T>
-__device__ __forceinline__ T* at(T* base, unsigned byte_off) {
-    return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte_off);
-}
-
-// Per-field base pointers, passed as kernel arguments so each one sits in
-// scalar registers and every access is that base plus one shared 32-bit
-// vector offset (no per-field 64-bit address arithmetic).
-template <class T>
-struct FieldPtrs {
-    const T* in[10];
-    T* out[10];
-    const float* g[3];
-};
-
-template <class S>
-__device__ __forceinline__ void load_node(const FieldPtrs<typename S::T>& f, unsigned n, const StepParams& p,
-                                          float m[10]) {
-    const unsigned off = n * (unsigned)sizeof(typename S::T);
-    m[0] = S::load(ld_at(f.in[0], off), p.inv_scale[0]);
-#pragma unroll
-    for (int q = 1; q < 4; ++q) m[q] = S::load(ld_at(f.in[q], off), p.inv_scale[1]);
-#pragma unroll
-    for (int q = 4; q < 10; ++q) m[q] = S::load(ld_at(f.in[q], off), p.inv_scale[2]);
-}
-
-// The stored values of node n, left unconverted: a caller that loads the
-// next plane ahead keeps them in flight until the plane's build converts
-// them (a conversion right after the loads would wait for them there).
-template <class S>
-__device__ __forceinline__ void load_raw(const FieldPtrs<typename S::T>& f, unsigned n, typename S::T r[10]) {
-    unsigned off = n * (unsigned)sizeof(typename S::T);
-    // keep the offset opaque so that each load is one scalar base plus this
-    // shared offset (no per-field 64-bit addresses carried across planes)
-    asm volatile("" : "+v"(off));
-#pragma unroll
-    for (int q = 0; q < 10; ++q) r[q] = ld_at(f.in[q], off);
-}
-
-// Converted values of load_raw.  drho and u get their scales; Pi^neq is
-// left unscaled: the caller folds 1 / scale[2] into 1 - omega, the only
-// factor Pi^neq meets in coefficients() (exact, a power of two).
-template <class S>
-__device__ __forceinline__ void convert_raw(const typename S::T r[10], const StepParams& p, float m[10]) {
-    m[0] = S::load(r[0], p.inv_scale[0]);
-#pragma unroll
-    for (int q = 1; q < 4; ++q) m[q] = S::load(r[q], p.inv_scale[1]);
-#pragma unroll
-    for (int q = 4; q < 10; ++q) m[q] = S::convert(r[q]);
 }
 
 // Plane index of zp in [-1, nz]: one wrap for a periodic axis, else clamp.
@@ -372,18 +309,6 @@ __device__ __forceinline__ bool upstream_solid(int wf, bool zlo, bool zhi) {
     if (Z == 1) s |= zlo;
     if (Z == -1) s |= zhi;
     return s;
-}
-
-template <class S>
-FieldPtrs<typename S::T> field_ptrs(const void* in, void* out, const StepParams& p) {
-    using T = typename S::T;
-    FieldPtrs<T> f;
-    for (int q = 0; q < 10; ++q) {
-        f.in[q] = (const T*)in + (size_t)q * p.geo.N;
-        f.out[q] = (T*)out + (size_t)q * p.geo.N;
-    }
-    for (int a = 0; a < 3; ++a) f.g[a] = p.gfield ? p.gfield + (size_t)a * p.geo.N : nullptr;
-    return f;
 }
 
 // Blocks of the tiled kernels that one CU holds at once: bounded by LDS

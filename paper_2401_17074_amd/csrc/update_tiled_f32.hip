@@ -1,0 +1,9 @@
+// FP32-storage instantiations of the tiled update.
+#include "update_tiled_kernel.h"
+
+namespace tslb {
+hipError_t launch_update_tiled_f32(const void* in, void* out, const StepParams& p, hipStream_t s) {
+    return launch_s<StoreF32>(in, out, p, s);
+}
+bool tiled_writes_x_ghosts_f32(const StepParams& p) { return writes_x_ghosts<StoreF32>(p); }
+}  // namespace tslb

@@ -1,0 +1,84 @@
+"""The tiled update where its tile rows, segments and wave roles meet an edge:
+grids narrower than a tile row, one or two columns past one, rows of whole
+cache lines and not; segments of a single plane (only their two halo planes
+and one output plane) and of several; walls and ghost faces on x.
+
+One step from a state that is representable in the storage format, against
+the oracle's FP64 step rounded to storage.  Bar: one storage ulp of the
+expected value (16-bit storage) plus 16 binary32 ulps of the largest
+magnitude of the field (for rho - 1 also of |u|, for Pi also of |u|^2: the
+terms that cancel in them).  Walls must stay at rest and ghosts hold their
+neighbour's values, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from helpers import from_device_state, gpu_solver, oracle_grid, to_device_state
+
+pytestmark = pytest.mark.gpu
+
+SCALES = {0: (1.0, 1.0, 1.0), 1: (2.0 ** 12, 2.0 ** 12, 2.0 ** 16), 2: (1.0, 1.0, 1.0)}
+FRAC_BITS, EMIN = {1: 10, 2: 7}, {1: -14, 2: -126}
+EPS32 = float(np.finfo(np.float32).eps)
+P, X, O = W.PERIODIC, W.WALL, W.OUTLET
+
+
+def _scaled(st, sc):
+    out = st.copy()
+    out[0] = (st[0] - 1.0) * sc[0]
+    out[1:4] *= sc[1]
+    out[4:] *= sc[2]
+    return out
+
+
+def _stored(G, st, kind, sc):
+    return oracle.round_storage(G, st, kind, sc) if kind else st
+
+
+def _check(kind, nx, ny, nz, xface):
+    # y walls with x walls, ghosts on z with x ghosts
+    faces = {P: (P,) * 6, X: (X, X, X, X, P, P), O: (O, O, P, P, O, O)}[xface]
+    case = W.Case("edges", nx, ny, nz, 0.61, faces=faces, force=(2e-6, 1e-6, 0.0))
+    G, sc = oracle_grid(case), SCALES[kind]
+    kinds = oracle.node_kinds(G)
+    st0 = W.to_fp32(W.random_state(case.shape, seed=41 + nx, u_amp=0.05, pi_amp=2e-3))
+    st0 = _stored(G, st0, kind, sc)
+    st0[:, kinds == 1] = W.rest_state((1,))[:, 0:1]
+    s = gpu_solver(case, storage=kind)
+    s.set_state(to_device_state(st0))
+    start = from_device_state(s.get_state())  # ghosts refilled
+    s.step(1)
+    got = from_device_state(s.get_state())
+    s.close()
+    want = oracle.step(G, start)
+    fl = kinds == 0
+    w, g = _scaled(_stored(G, want, kind, sc), sc)[:, fl], _scaled(got, sc)[:, fl]
+    ulp = 0.0
+    if kind:
+        ax = np.abs(w)
+        ulp = 2.0 ** (np.maximum(np.floor(np.log2(np.where(ax > 0, ax, 1.0))), EMIN[kind]) - FRAC_BITS[kind])
+    u, u2 = np.abs(want[1:4][:, fl]).max(), (want[1:4][:, fl] ** 2).sum(axis=0).max()
+    size = [max(np.abs(want[0][fl] - 1.0).max(), u) * sc[0]] + [u * sc[1]] * 3 + \
+        [max(np.abs(want[4:][:, fl]).max(), u2) * sc[2]] * 6
+    bar = 1.0000001 * ulp + 16 * EPS32 * np.array(size)[:, None]
+    assert np.all(np.abs(g - w) <= bar), float((np.abs(g - w) - bar).max())
+    assert np.array_equal(got[:, kinds == 1], np.broadcast_to(W.rest_state((1,))[:, 0:1], got[:, kinds == 1].shape))
+    if xface == O:
+        assert np.array_equal(got[:, :, :, 0], got[:, :, :, 1]) and np.array_equal(got[:, :, :, -1], got[:, :, :, -2])
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2])
+@pytest.mark.parametrize("nx", [1, 3, 63, 64, 65, 130])
+@pytest.mark.parametrize("xface", [P, X, O])
+def test_one_step(kind, nx, xface):
+    if xface != P and nx < 3:
+        pytest.skip("a non-periodic axis needs 3 nodes")
+    _check(kind, nx, 13, 5, xface)  # 13 rows: one past a tile of 12
+
+
+# 11 tile columns on 256 blocks: segments of 9, 8 and fewer planes
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("xface", [P, X, O])
+def test_longer_segments(kind, xface):
+    _check(kind, 66, 70, 203, xface)
