@@ -42,7 +42,9 @@ inline bool ghost_kind(int k) { return k == TSLB_INLET || k == TSLB_OUTLET; }
 hipError_t run_update(tslb_ctx* h, const void* in, void* out, hipStream_t s) {
     if (h->lattice == TSLB_D2Q9) return launch_update_d2q9(h->storage, in, out, h->p, s);
     switch (h->kernel) {
-    case 0: return launch_update_tiled(h->storage, in, out, h->p, s);
+    case 0:
+        return h->brick ? launch_update_brick(h->storage, in, out, h->p, s)
+                        : launch_update_tiled(h->storage, in, out, h->p, s);
     case 1: return launch_update_direct(h->storage, in, out, h->p, s);
     case 2: return launch_update_poplayout(h->storage, in, out, h->pop, h->p, s);
     }
@@ -72,8 +74,8 @@ int ensure_staging(tslb_ctx* h) {
 // tiled D3 update may already have refilled the plain x-face ghost nodes
 int fill_ghosts(tslb_ctx* h, void* st, hipStream_t s, bool after_update = false) {
     if (!h->has_ghosts) return TSLB_OK;
-    const int x_done = after_update && h->kernel == 0 && h->lattice != TSLB_D2Q9 &&
-                       tslb::tiled_writes_x_ghosts(h->storage, h->p);
+    const int x_done = after_update && h->kernel == 0 && h->lattice != TSLB_D2Q9 && !h->brick &&
+                       tiled_writes_x_ghosts(h->storage, h->p);
     HIP_TRY(launch_ghost_fill(h->storage, st, h->p, h->inlet, h->t, x_done, s));
     return TSLB_OK;
 }
@@ -194,7 +196,8 @@ int tslb_create(int nx, int ny, int nz, int lattice, float tau, const float forc
         // work list of the tiled update for this grid and this GPU
         std::vector<int4> seg;
         int grid = 0, nseg = 0;
-        if (tiled_schedule(g, seg, grid, nseg) != hipSuccess) {
+        long long steps = 0;
+        if (tiled_schedule(g, seg, grid, nseg, steps) != hipSuccess) {
             tslb_destroy(h);
             return fail(TSLB_E_INVALID, "no work list for the tiled update of this grid");
         }
@@ -209,6 +212,7 @@ int tslb_create(int nx, int ny, int nz, int lattice, float tau, const float forc
         h->p.sched = h->sched;
         h->p.sched_grid = grid;
         h->p.sched_nseg = nseg;
+        h->brick = prefers_brick(g, steps);
     }
     // rest state: drho = 0, u = 0, Pi = 0 in every format is all-zero bits
     if (hipMemset(h->buf[0], 0, bytes) != hipSuccess || hipMemset(h->buf[1], 0, bytes) != hipSuccess ||

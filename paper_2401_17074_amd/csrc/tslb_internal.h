@@ -17,7 +17,11 @@ hipError_t launch_update_direct(int storage, const void* in, void* out, const St
 hipError_t launch_update_poplayout(int storage, const void* in, void* out, float* pop, const StepParams& p,
                                    hipStream_t s);
 // Work list of the tiled update for grid g (host-side, see tile::Schedule).
-hipError_t tiled_schedule(const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg);
+hipError_t tiled_schedule(const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, long long& steps);
+// Update of small grids; does it beat the tiled update on grid g, whose work
+// list takes `steps` plane-steps?
+bool prefers_brick(const Geometry& g, long long steps);
+hipError_t launch_update_brick(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
 hipError_t launch_update_tiled(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
 hipError_t launch_update_d2q9(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
 int stats_blocks_per_plane(const Geometry& g, int axis);
@@ -87,4 +91,5 @@ struct tslb_ctx {
     double* stats_field;     // 9 N sums
     bool has_ghosts;
     int4* sched;             // work list of the tiled update (owned)
+    bool brick;              // small grid: the brick update in place of the tiled one
 };

@@ -268,6 +268,30 @@ __device__ __forceinline__ void store_out(P p, T v) {
         *p = v;
 }
 
+// A plane's address in one field, stepped from field to field, and a lane's
+// byte offset in the plane.  The address is kept as a scalar and made opaque
+// at each step (and the offset here), so that every access is this scalar
+// plus the 32-bit offset: left alone, the compiler keeps one address per
+// field across the plane loop (and spills them) or forms them with 64-bit
+// vector arithmetic.
+struct FieldAddress {
+    uint64_t at;
+    unsigned off;
+    template <class P>
+    __device__ __forceinline__ FieldAddress(P* plane, unsigned lane_off)
+        : at(reinterpret_cast<uint64_t>(plane)), off(lane_off) {
+        asm volatile("" : "+s"(at), "+v"(off));
+    }
+    __device__ __forceinline__ void next(size_t stride) {
+        at += stride;
+        asm volatile("" : "+s"(at));
+    }
+    template <class T>
+    __device__ __forceinline__ __attribute__((address_space(1))) T* lane() const {
+        return reinterpret_cast<__attribute__((address_space(1))) T*>(at + off);
+    }
+};
+
 // Plane index of zp in [-1, nz]: one wrap for a periodic axis, else clamp.
 __device__ __forceinline__ int plane_index(int zp, int nz, bool periodic) {
     if (periodic) return zp < 0 ? zp + nz : (zp >= nz ? zp - nz : zp);

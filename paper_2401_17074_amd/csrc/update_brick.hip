@@ -1,0 +1,249 @@
+// Brick update kernel for gfx950: the update of small grids.
+//
+// The tiled update marches 64 x 12 columns along z, a plane per step; on a
+// grid of a few hundred thousand nodes most of its time is the chain of those
+// steps (load, build, exchange, sum: more than a microsecond each) on too few
+// blocks.  Here one block updates a brick of BX x BY x BZ nodes at once: four
+// waves hold its nodes, seven more its one-node halo; each thread builds its
+// node's populations (a halo node the nine that can enter the brick) and
+// publishes them in LDS, and after one barrier the four waves gather the
+// arriving values of their nodes, sum and store.  One load latency, one
+// exchange, no serial chain; the price is 648 nodes built for 256 updated,
+// which is why the marching kernel takes over on larger grids (see
+// prefers_brick).
+#include "tslb_tiles.h"
+
+namespace tslb {
+namespace {
+
+using namespace tile;
+
+constexpr int BX = 16, BY = 4, BZ = 4;
+constexpr int HX = BX + 2, HY = BY + 2, HZ = BZ + 2;
+constexpr int kBrickNodes = HX * HY * HZ;  // with the halo
+constexpr int kBrickOut = BX * BY * BZ;
+// 4 waves of the brick's nodes, 2 of the z faces, 2 of the y faces, 1 of the
+// four edges along x, 2 of the x faces with all their edges and corners
+constexpr int kBrickThreads = kBrickOut + 2 * 64 + 2 * 64 + 64 + 128;
+static_assert(BX * BY == 64 && BX * BZ == 64 && 4 * BX == 64 && 2 * HY * HZ <= 128, "whole wavefronts per role");
+static_assert(27 * kBrickNodes * 4 * 2 <= 163840, "two bricks per CU");
+
+// In-range index of coordinate v >= -1 (periodic axes wrap, others clamp;
+// clamped values are never used by a fluid node).
+__device__ __forceinline__ int brick_index(int v, int n, bool periodic) {
+    if (!periodic) return min(max(v, 0), n - 1);
+    if (v < 0) v += n;
+    while (v >= n) v -= n;  // once, or more on an axis shorter than a brick
+    return v;
+}
+
+template <class S, bool WALLS, int ORDER, int LAT>
+__global__ void __launch_bounds__(kBrickThreads, 6)
+    update_brick_kernel(const char* __restrict__ in, char* __restrict__ out, StepParams p, int bricks_x, int bricks_y,
+                        int bricks) {
+    using T = typename S::T;
+    constexpr unsigned kSize = sizeof(T);
+    constexpr bool kDeferWeights = LAT == 27;
+    __shared__ float lds[27][kBrickNodes];
+    const Geometry& g = p.geo;
+    const size_t stride = (size_t)g.N * kSize;
+    // each XCD takes a contiguous run of bricks (block ids go round-robin)
+    const int per = (int)(gridDim.x >> 3);
+    const int b = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if (b >= bricks) return;  // padding block, before the barrier
+    const int x0 = b % bricks_x * BX, y0 = b / bricks_x % bricks_y * BY, z0 = b / (bricks_x * bricks_y) * BZ;
+    const int tid = threadIdx.x;
+
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // coordinates in the brick with its halo
+    enum { kNode, kZ, kY, kX };
+    int hx, hy, hz, role = kNode;
+    bool on = true;
+    if (wave < 4) {
+        hx = 1 + (lane & (BX - 1));
+        hy = 1 + lane / BX;
+        hz = 1 + wave;
+    } else if (wave < 6) {
+        role = kZ;
+        hx = 1 + (lane & (BX - 1));
+        hy = 1 + lane / BX;
+        hz = wave == 4 ? 0 : HZ - 1;
+    } else if (wave < 8) {
+        role = kY;
+        hx = 1 + (lane & (BX - 1));
+        hy = wave == 6 ? 0 : HY - 1;
+        hz = 1 + lane / BX;
+    } else if (wave == 8) {
+        role = kZ;  // an edge along x
+        hx = 1 + (lane & (BX - 1));
+        hy = (lane & BX) ? HY - 1 : 0;
+        hz = (lane & (2 * BX)) ? HZ - 1 : 0;
+    } else {
+        role = kX;
+        const int k = (wave - 9) * 64 + lane;  // 36 nodes at each end
+        on = k < 2 * HY * HZ;
+        hx = k < HY * HZ ? 0 : HX - 1;
+        hy = k % HY;
+        hz = k / HY % HZ;
+    }
+    float G[27];
+    const int x = x0 - 1 + hx, y = y0 - 1 + hy, z = z0 - 1 + hz;
+    const int own = hx + HX * (hy + HY * hz);
+    if (on) {
+        const int wx = brick_index(x, g.n[0], g.periodic & 1);
+        const int wy = brick_index(y, g.n[1], g.periodic & 2);
+        const int wz = brick_index(z, g.n[2], g.periodic & 4);
+        const unsigned n = (unsigned)wx + (unsigned)g.n[0] * ((unsigned)wy + (unsigned)g.n[1] * (unsigned)wz);
+        T r[10];
+        FieldAddress f(in, n * kSize);
+#pragma unroll
+        for (int q = 0; q < 10; ++q) {
+            r[q] = __builtin_bit_cast(T, *f.template lane<const store_bits<T>>());
+            f.next(stride);
+        }
+        float gl[3] = {p.force[0], p.force[1], p.force[2]};
+        if (p.gfield) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) gl[a] = p.gfield[(size_t)a * g.N + n];
+        }
+        // wall nodes emit nothing: they hold the rest state, and no force
+        if (WALLS && is_solid(g, wx, wy, wz)) gl[0] = gl[1] = gl[2] = 0.0f;
+        float m[10];
+        m[0] = S::load(r[0], p.inv_scale[0]);
+#pragma unroll
+        for (int q = 1; q < 4; ++q) m[q] = S::load(r[q], p.inv_scale[1]);
+#pragma unroll
+        for (int q = 4; q < 10; ++q) m[q] = S::convert(r[q]);
+        // 1 - omega takes the stored Pi^neq scale
+        const float omo = omo_at(p, wz);
+        float A[NK];
+        coefficients<ORDER, LAT>(m, gl, kSize == 4 ? omo : omo * p.inv_scale[2], A);
+        // what a halo node sends into the brick has one velocity component
+        // fixed at s = +-1: the polynomial in the two others, on their 3 x 3
+        // grid Q[18 + 3 (later) + (earlier)]
+        float* const w = &lds[0][own];
+        auto put = [&]<int I>(float* base, float v, bool carried) {
+            if (carried) base[I * kBrickNodes] = v;
+        };
+        if (role == kNode) {
+            populations<LAT, !kDeferWeights>(A, G);
+            Unroll<0, 27>::run([&]<int I>() {
+                if constexpr (carries<LAT>(I) && I != 13) w[I * kBrickNodes] = G[I];
+            });
+        } else if (role == kZ) {
+            const float s = hz == 0 ? 1.0f : -1.0f;
+            eval_slice<1, LAT, !kDeferWeights>(fmaf(s, A[K001], A[K000] + A[K002]), fmaf(s, A[K101], A[K100] + A[K102]),
+                                               fmaf(s, A[K011], A[K010] + A[K012]), fmaf(s, A[K201], A[K200]),
+                                               fmaf(s, A[K021], A[K020]), fmaf(s, A[K111], A[K110]), A[K210], A[K120],
+                                               G);
+            float* const b9 = w + (hz == 0 ? 18 : 0) * kBrickNodes;
+            Unroll<0, 9>::run([&]<int I>() { put.template operator()<I>(b9, G[18 + I], carries<LAT>(18 + I)); });
+        } else if (role == kY) {
+            const float s = hy == 0 ? 1.0f : -1.0f;
+            eval_slice<1, LAT, !kDeferWeights>(fmaf(s, A[K010], A[K000] + A[K020]), fmaf(s, A[K110], A[K100] + A[K120]),
+                                               fmaf(s, A[K011], A[K001] + A[K021]), fmaf(s, A[K210], A[K200]),
+                                               fmaf(s, A[K012], A[K002]), fmaf(s, A[K111], A[K101]), A[K201], A[K102],
+                                               G);
+            float* const b9 = w + (hy == 0 ? 6 : 0) * kBrickNodes;
+            Unroll<0, 9>::run([&]<int I>() {
+                put.template operator()<9 * (I / 3) + I % 3>(b9, G[18 + I], carries<LAT>(9 * (I / 3) + I % 3));
+            });
+        } else {
+            const float s = hx == 0 ? 1.0f : -1.0f;
+            eval_slice<1, LAT, !kDeferWeights>(fmaf(s, A[K100], A[K000] + A[K200]), fmaf(s, A[K110], A[K010] + A[K210]),
+                                               fmaf(s, A[K101], A[K001] + A[K201]), fmaf(s, A[K120], A[K020]),
+                                               fmaf(s, A[K102], A[K002]), fmaf(s, A[K111], A[K011]), A[K021], A[K012],
+                                               G);
+            float* const b9 = w + (hx == 0 ? 2 : 0) * kBrickNodes;
+            Unroll<0, 9>::run([&]<int I>() {
+                put.template operator()<9 * (I / 3) + 3 * (I % 3)>(b9, G[18 + I], carries<LAT>(9 * (I / 3) + 3 * (I % 3)));
+            });
+        }
+    }
+    __syncthreads();
+    if (role != kNode) return;
+    if (x >= g.n[0] || y >= g.n[1] || z >= g.n[2] || !is_fluid(g, x, y, z)) return;
+    const int wf = WALLS ? wall_flags(g, x, y) : 0;
+    const bool zlo = WALLS && (g.lo_solid & 4) && z == 1, zhi = WALLS && (g.hi_solid & 4) && z == g.n[2] - 2;
+    float F[3][3][3];  // [cz + 1][cy + 1][cx + 1]
+    Unroll<0, 27>::run([&]<int I>() {
+        constexpr int X = cx_of(I), Y = cy_of(I), Z = cz_of(I);
+        if constexpr (!carries<LAT>(I))
+            F[Z + 1][Y + 1][X + 1] = 0.0f;
+        else if constexpr (I == 13)
+            F[1][1][1] = G[13];
+        else
+            F[Z + 1][Y + 1][X + 1] = lds[I][own - X - HX * (Y + HY * Z)];
+    });
+    if (WALLS && (wf != 0 || zlo || zhi)) {
+        // half-way bounce-back: the node's own population along -c comes back
+        // where the upstream node is a wall (of equal weight)
+        Unroll<0, 27>::run([&]<int I>() {
+            if (upstream_solid<I>(wf, zlo, zhi)) F[cz_of(I) + 1][cy_of(I) + 1][cx_of(I) + 1] = G[26 - I];
+        });
+    }
+    MomentSums a;
+    add_slice<1, true, kDeferWeights>(F[2], a);
+    add_slice<0, false, kDeferWeights>(F[1], a);
+    add_slice<-1, false, kDeferWeights>(F[0], a);
+    float o[10];
+    finalize<LAT == 19 ? 36 : 216>(a, o);
+    const unsigned n = (unsigned)x + (unsigned)g.n[0] * ((unsigned)y + (unsigned)g.n[1] * (unsigned)z);
+    FieldAddress f(out, n * kSize);
+#pragma unroll
+    for (int q = 0; q < 10; ++q) {
+        *f.template lane<store_bits<T>>() =
+            __builtin_bit_cast(store_bits<T>, S::store(o[q], p.scale[q == 0 ? 0 : q < 4 ? 1 : 2]));
+        f.next(stride);
+    }
+}
+
+template <class S, bool WALLS, int ORDER, int LAT>
+hipError_t launch_k(const void* in, void* out, const StepParams& p, hipStream_t s) {
+    const int bx = (p.geo.n[0] + BX - 1) / BX, by = (p.geo.n[1] + BY - 1) / BY, bz = (p.geo.n[2] + BZ - 1) / BZ;
+    const long long bricks = (long long)bx * by * bz;
+    if (p.geo.N >= (1LL << 30) || bricks > (1 << 24)) return hipErrorInvalidValue;
+    const unsigned grid = (unsigned)((bricks + 7) & ~7LL);  // whole runs per XCD
+    hipLaunchKernelGGL((update_brick_kernel<S, WALLS, ORDER, LAT>), dim3(grid), dim3(kBrickThreads), 0, s,
+                       (const char*)in, (char*)out, p, bx, by, (int)bricks);
+    return hipGetLastError();
+}
+
+template <class S, int ORDER, int LAT>
+hipError_t launch_w(const void* in, void* out, const StepParams& p, hipStream_t s) {
+    return (p.geo.lo_solid | p.geo.hi_solid) != 0 ? launch_k<S, true, ORDER, LAT>(in, out, p, s)
+                                                  : launch_k<S, false, ORDER, LAT>(in, out, p, s);
+}
+
+template <class S>
+hipError_t launch_s(const void* in, void* out, const StepParams& p, hipStream_t s) {
+    if (p.lattice == 19) return p.order == 2 ? launch_w<S, 2, 19>(in, out, p, s) : launch_w<S, 3, 19>(in, out, p, s);
+    return p.order == 2 ? launch_w<S, 2, 27>(in, out, p, s) : launch_w<S, 3, 27>(in, out, p, s);
+}
+
+}  // namespace
+
+// Bricks run in rounds of one per CU (two at a time), a round about 1.6 us
+// after the first 4.6; the marching kernel takes about 5 us and 1.1 us for
+// each plane-step of its longest block (steps: the work list's cost).  us per
+// step of an FP32 periodic grid, marching / bricks: 32^3 (1 round, 3 steps)
+// 8.3 / 4.6, 48^3 (2, 3) 8.7 / 6.0, 50^3 (3, 3) 8.2 / 8.8, 56^3 (4, 4) 10.0 /
+// 9.4, 16 x 90 x 90 (3, 5) 11.3 / 7.4, 64^3 (4, 4) 10.5 / 11.0, 96^3 (14, 8)
+// 21.2 / 27.9.
+bool prefers_brick(const Geometry& g, long long steps) {
+    const long long bricks = (long long)((g.n[0] + BX - 1) / BX) * ((g.n[1] + BY - 1) / BY) * ((g.n[2] + BZ - 1) / BZ);
+    const long long rounds = (bricks + compute_units() - 1) / compute_units();
+    return rounds < steps;
+}
+
+hipError_t launch_update_brick(int storage, const void* in, void* out, const StepParams& p, hipStream_t s) {
+    switch (storage) {
+    case 0: return launch_s<StoreF32>(in, out, p, s);
+    case 1: return launch_s<StoreF16>(in, out, p, s);
+    case 2: return launch_s<StoreBF16>(in, out, p, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace tslb

@@ -5,7 +5,7 @@ namespace tslb {
 
 using namespace tile;
 
-hipError_t tiled_schedule(const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg) {
+hipError_t tiled_schedule(const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, long long& steps) {
     const int columns = ((g.n[0] + TX - 1) / TX) * ((g.n[1] + TY - 1) / TY);
     const int resident = (compute_units() * kBlocksPerCu + 7) & ~7;
     Schedule s = build_schedule(columns, g.n[2], resident);
@@ -13,6 +13,7 @@ hipError_t tiled_schedule(const Geometry& g, std::vector<int4>& seg, int& grid, 
     seg = std::move(s.seg);
     grid = s.grid;
     nseg = s.nseg;
+    steps = s.cost;
     return hipSuccess;
 }
 

@@ -61,30 +61,6 @@ using namespace tile;
 // in its lower half).
 template <class S>
 using raw_t = std::conditional_t<sizeof(typename S::T) == 4, float, unsigned>;
-// A plane's address in one field, stepped from field to field, and a lane's
-// byte offset in the plane.  The address is kept as a scalar and made opaque
-// at each step (and the offset here), so that every access is this scalar
-// plus the 32-bit offset: left alone, the compiler keeps one address per
-// field across the plane loop (and spills them) or forms them with 64-bit
-// vector arithmetic.
-struct FieldAddress {
-    uint64_t at;
-    unsigned off;
-    template <class P>
-    __device__ __forceinline__ FieldAddress(P* plane, unsigned lane_off)
-        : at(reinterpret_cast<uint64_t>(plane)), off(lane_off) {
-        asm volatile("" : "+s"(at), "+v"(off));
-    }
-    __device__ __forceinline__ void next(size_t stride) {
-        at += stride;
-        asm volatile("" : "+s"(at));
-    }
-    template <class T>
-    __device__ __forceinline__ __attribute__((address_space(1))) T* lane() const {
-        return reinterpret_cast<__attribute__((address_space(1))) T*>(at + off);
-    }
-};
-
 // Loads the ten fields at byte offset `off` of the plane at `plane`;
 // consecutive fields are `stride` bytes apart.
 template <class S>

@@ -1,7 +1,8 @@
-"""The tiled update where its tile rows, segments and wave roles meet an edge:
-grids narrower than a tile row, one or two columns past one, rows of whole
-cache lines and not; segments of a single plane (only their two halo planes
-and one output plane) and of several; walls and ghost faces on x.
+"""The tiled and the brick update where their tiles, segments, bricks and wave
+roles meet an edge: rows narrower than a tile or a brick, one or two columns
+past one, rows of whole cache lines and not; segments of a single plane (only
+their two halo planes and one output plane) and of several; walls and ghost
+faces on x.  Small grids run the brick kernel, the larger ones here the tiled.
 
 One step from a state that is representable in the storage format, against
 the oracle's FP64 step rounded to storage.  Bar: one storage ulp of the
@@ -68,17 +69,49 @@ def _check(kind, nx, ny, nz, xface):
         assert np.array_equal(got[:, :, :, 0], got[:, :, :, 1]) and np.array_equal(got[:, :, :, -1], got[:, :, :, -2])
 
 
+# bricks of 16 x 4 x 4: 13 rows and 5 planes are one past a brick
 @pytest.mark.parametrize("kind", [0, 1, 2])
-@pytest.mark.parametrize("nx", [1, 3, 63, 64, 65, 130])
+@pytest.mark.parametrize("nx", [1, 3, 15, 16, 17, 33])
 @pytest.mark.parametrize("xface", [P, X, O])
-def test_one_step(kind, nx, xface):
+def test_bricks(kind, nx, xface):
     if xface != P and nx < 3:
         pytest.skip("a non-periodic axis needs 3 nodes")
-    _check(kind, nx, 13, 5, xface)  # 13 rows: one past a tile of 12
+    _check(kind, nx, 13, 5, xface)
 
 
-# 11 tile columns on 256 blocks: segments of 9, 8 and fewer planes
+# tiles of 64 x 12, 37 rows one past a tile, segments of one and two planes
+@pytest.mark.parametrize("kind", [0, 1, 2])
+@pytest.mark.parametrize("nx", [63, 64, 65, 130])
+@pytest.mark.parametrize("xface", [P, X, O])
+def test_tiles(kind, nx, xface):
+    _check(kind, nx, 37, 101, xface)
+
+
+# 12 tile columns on 256 blocks: segments of 9, 8 and fewer planes
 @pytest.mark.parametrize("kind", [0, 1])
 @pytest.mark.parametrize("xface", [P, X, O])
 def test_longer_segments(kind, xface):
     _check(kind, 66, 70, 203, xface)
+
+
+@pytest.mark.parametrize("lattice,order", [(19, 3), (27, 2), (19, 2)])
+@pytest.mark.parametrize("dims", [(17, 13, 9), (66, 37, 101)])
+def test_other_lattice_and_order(lattice, order, dims):
+    """Force field and walls with D3Q19 and order 2."""
+    faces = (P, P, X, X, X, X)
+    case = W.Case("lat", *dims, 0.61, faces=faces, lattice=lattice, order=order)
+    G = oracle_grid(case)
+    kinds = oracle.node_kinds(G)
+    st0 = W.to_fp32(W.random_state(case.shape, seed=7, u_amp=0.05, pi_amp=2e-3))
+    st0[:, kinds == 1] = W.rest_state((1,))[:, 0:1]
+    g = W.random_force(case.shape, seed=8, amp=2e-6).astype(np.float32).astype(np.float64)
+    s = gpu_solver(case)
+    s.set_force_field(g)
+    s.set_state(to_device_state(st0))
+    s.step(1)
+    got, want = from_device_state(s.get_state()), oracle.step(G, st0, g)
+    s.close()
+    fl = kinds == 0
+    u, u2 = np.abs(want[1:4][:, fl]).max(), (want[1:4][:, fl] ** 2).sum(axis=0).max()
+    size = [max(np.abs(want[0][fl] - 1.0).max(), u)] + [u] * 3 + [max(np.abs(want[4:][:, fl]).max(), u2)] * 6
+    assert np.all(np.abs(got - want)[:, fl] <= 16 * EPS32 * np.array(size)[:, None])
