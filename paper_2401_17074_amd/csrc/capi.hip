@@ -197,7 +197,7 @@ int tslb_create(int nx, int ny, int nz, int lattice, float tau, const float forc
         std::vector<int4> seg;
         int grid = 0, nseg = 0;
         long long steps = 0;
-        if (tiled_schedule(g, seg, grid, nseg, steps) != hipSuccess) {
+        if (tiled_schedule(h->storage, g, seg, grid, nseg, steps) != hipSuccess) {
             tslb_destroy(h);
             return fail(TSLB_E_INVALID, "no work list for the tiled update of this grid");
         }

@@ -16,8 +16,9 @@ namespace tslb {
 hipError_t launch_update_direct(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
 hipError_t launch_update_poplayout(int storage, const void* in, void* out, float* pop, const StepParams& p,
                                    hipStream_t s);
-// Work list of the tiled update for grid g (host-side, see tile::Schedule).
-hipError_t tiled_schedule(const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, long long& steps);
+// Work list of the tiled update for grid g and a storage format (host-side,
+// see tile::Schedule).
+hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, long long& steps);
 // Update of small grids; does it beat the tiled update on grid g, whose work
 // list takes `steps` plane-steps?
 bool prefers_brick(const Geometry& g, long long steps);

@@ -5,5 +5,6 @@ namespace tslb {
 hipError_t launch_update_tiled_f32(const void* in, void* out, const StepParams& p, hipStream_t s) {
     return launch_s<StoreF32>(in, out, p, s);
 }
+int tiled_columns_f32(const Geometry& g) { return tile_columns(g); }
 bool tiled_writes_x_ghosts_f32(const StepParams& p) { return writes_x_ghosts<StoreF32>(p); }
 }  // namespace tslb

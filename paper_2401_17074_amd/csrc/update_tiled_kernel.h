@@ -539,6 +539,9 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
     }
 }
 
+// Tile columns of a grid.
+inline int tile_columns(const Geometry& g) { return ((g.n[0] + TX - 1) / TX) * ((g.n[1] + TY - 1) / TY); }
+
 template <class S>
 bool rows_whole_lines(const StepParams& p) {
     return ((long long)p.geo.n[0] * (long long)sizeof(typename S::T)) % 128 == 0;
