@@ -181,6 +181,15 @@ def tslb_stats_profile(h, n_axis, stream=None):
     return [list(buf[13 * j:13 * j + 13]) for j in range(n_axis)], ns.value
 
 
+def tslb_stats_profile_into(h, sums, stream=None):
+    """tslb_stats_profile into a contiguous float64 host tensor of 13 n_axis
+    values; returns the number of samples."""
+    ns = ctypes.c_int64()
+    _check(lib.tslb_stats_profile(h, ctypes.cast(sums.data_ptr(), ctypes.POINTER(_d)), ctypes.byref(ns),
+                                  _stream(stream)))
+    return ns.value
+
+
 def tslb_stats_field(h, mean_u, cov, stream=None):
     return _check(lib.tslb_stats_field(h, _ptr(mean_u), _ptr(cov), _stream(stream)))
 

@@ -167,21 +167,17 @@ __global__ void __launch_bounds__(kRedThreads) reduce_partial_kernel(const typen
         for (int k = 0; k < kRedSums; ++k) partials[k * gridDim.x + blockIdx.x] = sh[k][0];
 }
 
-__global__ void __launch_bounds__(kRedThreads) reduce_final_kernel(const double* __restrict__ partials, int nblocks,
-                                                                   double* __restrict__ out6) {
-    __shared__ double sh[kRedThreads];
-    for (int k = 0; k < kRedSums; ++k) {
-        double a = 0.0;
-        for (int b = threadIdx.x; b < nblocks; b += blockDim.x) a += partials[k * nblocks + b];
-        sh[threadIdx.x] = a;
-        __syncthreads();
-        for (int w = kRedThreads / 2; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) out6[k] = sh[0];
-        __syncthreads();
-    }
+// One wave per sum (one block of 256 threads doing the seven sums in turn
+// took 14 us).
+__global__ void __launch_bounds__(64 * kRedSums) reduce_final_kernel(const double* __restrict__ partials, int nblocks,
+                                                                     double* __restrict__ out6) {
+    const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double a = 0.0;
+#pragma unroll 4
+    for (int b = lane; b < nblocks; b += 64) a += partials[k * nblocks + b];
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) a += __shfl_xor(a, w);
+    if (lane == 0) out6[k] = a;
 }
 
 // ---------------------------------------------------------------- adjoint
@@ -491,7 +487,7 @@ hipError_t launch_reduce(int storage, const void* st, double* partials, int nblo
     case 2: hipLaunchKernelGGL(reduce_partial_kernel<StoreBF16>, dim3(nblocks), dim3(kRedThreads), 0, s, (const uint16_t*)st, partials, p); break;
     default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(reduce_final_kernel, dim3(1), dim3(kRedThreads), 0, s, partials, nblocks, out6);
+    hipLaunchKernelGGL(reduce_final_kernel, dim3(1), dim3(64 * kRedSums), 0, s, partials, nblocks, out6);
     return hipGetLastError();
 }
 

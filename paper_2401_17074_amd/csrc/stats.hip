@@ -6,11 +6,13 @@
 //   profile : for every index j along the profile axis, the sums over the
 //             fluid nodes of plane j of 1, u_a, u_a u_b, u_a^3 (13 values),
 //             accumulated over samples.  A sample is two launches: per-block
-//             partials in a fixed order, then one thread per (plane, value)
-//             adds them up in a fixed order (deterministic).
+//             partials in a fixed order, then one wave per plane adds them up
+//             in a fixed order (deterministic).
 //   field   : per-node sums of u_a and u_a u_b (9 FP64 arrays).
 //   jet     : one block per cross-section bins the mean axial velocity by
 //             k = floor(r) in LDS, then finds U_c and r_1/2.
+#include <algorithm>
+
 #include "tslb_internal.h"
 
 namespace tslb {
@@ -18,15 +20,19 @@ namespace {
 
 constexpr int kStatBlock = 256;
 
-// node index of in-plane position k of plane j along axis
-__device__ __forceinline__ long long plane_node(const Geometry& g, int axis, int j, long long k, int c[3]) {
-    const int d1 = axis == 0 ? 1 : 0, d2 = axis == 2 ? 1 : 2;
-    c[axis] = j;
-    c[d1] = (int)(k % g.n[d1]);
-    c[d2] = (int)(k / g.n[d1]);
-    return c[0] + (long long)g.n[0] * (c[1] + (long long)g.n[1] * c[2]);
+// Sum of v over the wave, in every lane, in a fixed order.
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) v += __shfl_xor(v, w);
+    return v;
 }
 
+// One plane's partial sums by one block.  A block's nodes are k, k + step, ...
+// of the plane (step = blocks_per_plane * kStatBlock), whose coordinates are
+// advanced instead of divided out.  What bounds it: the 12 bytes per node
+// read (384 x 192 x 192: 170 MB, 28 us at the copy rate); with 64-bit
+// divisions per node and a 13-value LDS tree for every four nodes of a thread
+// it took 68 us.
 template <class S>
 __global__ void __launch_bounds__(kStatBlock) profile_partial_kernel(const typename S::T* __restrict__ st,
                                                                      double* __restrict__ part, StepParams p,
@@ -34,56 +40,88 @@ __global__ void __launch_bounds__(kStatBlock) profile_partial_kernel(const typen
     const Geometry& g = p.geo;
     const int j = blockIdx.y;
     const int d1 = axis == 0 ? 1 : 0, d2 = axis == 2 ? 1 : 2;
-    const long long plane = (long long)g.n[d1] * g.n[d2];
+    const unsigned n1 = (unsigned)g.n[d1], n2 = (unsigned)g.n[d2];
+    const unsigned stride[3] = {1u, (unsigned)g.n[0], (unsigned)g.n[0] * (unsigned)g.n[1]};
     double acc[13];
 #pragma unroll
     for (int q = 0; q < 13; ++q) acc[q] = 0.0;
-    for (long long k = (long long)blockIdx.x * kStatBlock + threadIdx.x; k < plane;
-         k += (long long)blocks_per_plane * kStatBlock) {
-        int c[3];
-        const long long n = plane_node(g, axis, j, k, c);
-        if (!is_fluid(g, c[0], c[1], c[2])) continue;
-        const double u0 = S::load(st[1 * g.N + n], p.inv_scale[1]);
-        const double u1 = S::load(st[2 * g.N + n], p.inv_scale[1]);
-        const double u2 = S::load(st[3 * g.N + n], p.inv_scale[1]);
-        acc[0] += 1.0;
-        acc[1] += u0;
-        acc[2] += u1;
-        acc[3] += u2;
-        acc[4] += u0 * u0;
-        acc[5] += u1 * u1;
-        acc[6] += u2 * u2;
-        acc[7] += u0 * u1;
-        acc[8] += u0 * u2;
-        acc[9] += u1 * u2;
-        acc[10] += u0 * u0 * u0;
-        acc[11] += u1 * u1 * u1;
-        acc[12] += u2 * u2 * u2;
-    }
-    // block reduction in a fixed order
-    __shared__ double red[13][kStatBlock];
+    const unsigned step = (unsigned)blocks_per_plane * kStatBlock, step1 = step % n1, step2 = step / n1;
+    const unsigned k0 = blockIdx.x * kStatBlock + threadIdx.x;
+    unsigned c1 = k0 % n1, c2 = k0 / n1;
+    const bool plane_fluid = !(j == 0 && (((g.lo_solid | g.lo_ghost) >> axis) & 1)) &&
+                             !(j == g.n[axis] - 1 && (((g.hi_solid | g.hi_ghost) >> axis) & 1));
+    const unsigned lo1 = ((g.lo_solid | g.lo_ghost) >> d1) & 1, hi1 = n1 - (((g.hi_solid | g.hi_ghost) >> d1) & 1);
+    const unsigned lo2 = ((g.lo_solid | g.lo_ghost) >> d2) & 1, hi2 = n2 - (((g.hi_solid | g.hi_ghost) >> d2) & 1);
+    const auto* __restrict__ u0p = st + 1 * g.N;
+    const auto* __restrict__ u1p = st + 2 * g.N;
+    const auto* __restrict__ u2p = st + 3 * g.N;
+    while (plane_fluid && c2 < n2) {
+        // four nodes at a time, so that their loads are in flight together
+        typename S::T r[4][3];
+        bool on[4];
 #pragma unroll
-    for (int q = 0; q < 13; ++q) red[q][threadIdx.x] = acc[q];
-    __syncthreads();
-    for (int w = kStatBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-#pragma unroll
-            for (int q = 0; q < 13; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + w];
+        for (int e = 0; e < 4; ++e) {
+            on[e] = c2 < n2 && c1 >= lo1 && c1 < hi1 && c2 >= lo2 && c2 < hi2;
+            const unsigned n = on[e] ? (unsigned)j * stride[axis] + c1 * stride[d1] + c2 * stride[d2] : 0u;
+            r[e][0] = u0p[n];
+            r[e][1] = u1p[n];
+            r[e][2] = u2p[n];
+            c1 += step1;
+            c2 += step2;
+            if (c1 >= n1) {
+                c1 -= n1;
+                ++c2;
+            }
         }
-        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (!on[e]) continue;
+            const double u0 = S::load(r[e][0], p.inv_scale[1]);
+            const double u1 = S::load(r[e][1], p.inv_scale[1]);
+            const double u2 = S::load(r[e][2], p.inv_scale[1]);
+            acc[0] += 1.0;
+            acc[1] += u0;
+            acc[2] += u1;
+            acc[3] += u2;
+            acc[4] += u0 * u0;
+            acc[5] += u1 * u1;
+            acc[6] += u2 * u2;
+            acc[7] += u0 * u1;
+            acc[8] += u0 * u2;
+            acc[9] += u1 * u2;
+            acc[10] += u0 * u0 * u0;
+            acc[11] += u1 * u1 * u1;
+            acc[12] += u2 * u2 * u2;
+        }
     }
-    if (threadIdx.x < 13)
-        part[((long long)j * blocks_per_plane + blockIdx.x) * 13 + threadIdx.x] = red[threadIdx.x][0];
+    // block reduction in a fixed order: within each wave, then over the waves
+    __shared__ double red[kStatBlock / 64][13];
+#pragma unroll
+    for (int q = 0; q < 13; ++q) {
+        const double v = wave_sum(acc[q]);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 13) {
+        double v = red[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < kStatBlock / 64; ++w) v += red[w][threadIdx.x];
+        part[((long long)j * blocks_per_plane + blockIdx.x) * 13 + threadIdx.x] = v;
+    }
 }
 
-__global__ void profile_final_kernel(const double* __restrict__ part, double* __restrict__ sums, int n_axis,
-                                     int blocks_per_plane) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_axis * 13) return;
-    const int j = i / 13, q = i % 13;
+// One wave per plane: 16 lanes per group of partials (13 used), four groups
+// side by side, added in a fixed order (one thread per value, 64 partials one
+// after the other, took 20 us).
+__global__ void __launch_bounds__(64) profile_final_kernel(const double* __restrict__ part, double* __restrict__ sums,
+                                                           int blocks_per_plane) {
+    const int j = blockIdx.x, q = threadIdx.x & 15;
     double s = 0.0;
-    for (int b = 0; b < blocks_per_plane; ++b) s += part[((long long)j * blocks_per_plane + b) * 13 + q];
-    sums[i] += s;
+    if (q < 13)
+        for (int b = threadIdx.x >> 4; b < blocks_per_plane; b += 4) s += part[((long long)j * blocks_per_plane + b) * 13 + q];
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (threadIdx.x < 13) sums[(long long)j * 13 + q] += s;
 }
 
 template <class S>
@@ -208,8 +246,7 @@ hipError_t profile_s(const void* st, double* part, double* sums, const StepParam
                        (const typename S::T*)st, part, p, axis, bpp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int total = n_axis * 13;
-    hipLaunchKernelGGL(profile_final_kernel, dim3((total + 255) / 256), dim3(256), 0, s, part, sums, n_axis, bpp);
+    hipLaunchKernelGGL(profile_final_kernel, dim3(n_axis), dim3(64), 0, s, part, sums, bpp);
     return hipGetLastError();
 }
 
@@ -225,8 +262,11 @@ hipError_t field_s(const void* st, double* fs, const StepParams& p, hipStream_t 
 int stats_blocks_per_plane(const Geometry& g, int axis) {
     const int d1 = axis == 0 ? 1 : 0, d2 = axis == 2 ? 1 : 2;
     const long long plane = (long long)g.n[d1] * g.n[d2];
-    long long b = (plane + 4 * kStatBlock - 1) / (4 * kStatBlock);
-    return (int)(b < 1 ? 1 : (b > 64 ? 64 : b));
+    // 16 nodes per thread, fewer where that leaves the chip with under 2048
+    // blocks (eight per CU)
+    const long long per = std::max(4LL, std::min(16LL, plane * g.n[axis] / (2048LL * kStatBlock)));
+    const long long b = (plane + per * kStatBlock - 1) / (per * kStatBlock);
+    return (int)std::max(1LL, std::min(64LL, b));
 }
 
 hipError_t launch_stats_profile(int storage, const void* st, double* part, double* sums, const StepParams& p,

@@ -87,8 +87,9 @@ class Solver:
     def stats_profile(self):
         """(sums (n_axis, 13) float64 tensor on the host, number of samples)."""
         n_axis = (self.shape[2], self.shape[1], self.shape[0])[self._stats_axis]
-        rows, ns = C.tslb_stats_profile(self.h, n_axis)
-        return torch.tensor(rows, dtype=torch.float64), ns
+        rows = torch.empty((n_axis, 13), dtype=torch.float64)
+        ns = C.tslb_stats_profile_into(self.h, rows)
+        return rows, ns
 
     def stats_field(self):
         """Per-node mean velocity (3, nz, ny, nx) and covariances (6, ...)."""
