@@ -1,6 +1,8 @@
 // Kernels around the update: ghost-layer refill (Section 2.3), conversion
 // between caller arrays and the stored format, FP64 reductions, and the
 // discrete adjoint of one update step.
+#include <algorithm>
+
 #include "tslb_internal.h"
 
 namespace tslb {
@@ -66,9 +68,14 @@ __global__ void ghost_fill_kernel(typename S::T* __restrict__ st, StepParams p, 
 }
 
 // ---------------------------------------------------------------- pack/unpack
+// other: the handle's second state buffer.  A step writes its fluid and ghost
+// nodes before anything reads them, so only what no step writes is stored
+// there as well: the wall nodes and, in two dimensions, the z components
+// (the whole buffer was copied before: 160 bytes per node against 80).
 template <class S>
 __global__ void pack_kernel(const float* __restrict__ rho, const float* __restrict__ u, const float* __restrict__ pi,
-                            int rho_dev, typename S::T* __restrict__ st, StepParams p) {
+                            int rho_dev, typename S::T* __restrict__ st, typename S::T* __restrict__ other,
+                            StepParams p) {
     const Geometry& g = p.geo;
     const long long N = g.N;
     const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -80,16 +87,24 @@ __global__ void pack_kernel(const float* __restrict__ rho, const float* __restri
     const int z = (int)(n / ((long long)g.n[0] * g.n[1]));
     const float keep = is_solid(g, x, y, z) ? 0.0f : 1.0f;
     const float r = rho[n];
-    st[n] = S::store(keep * (rho_dev ? r : r - 1.0f), p.scale[0]);
+    const bool wall = keep == 0.0f;
+    auto put = [&](int k, float v, float scale, bool both) {
+        const typename S::T b = S::store(v, scale);
+        st[k * N + n] = b;
+        if (both) other[k * N + n] = b;
+    };
+    put(0, keep * (rho_dev ? r : r - 1.0f), p.scale[0], wall);
     // a two-dimensional lattice keeps u_z and the Pi components with a z
     // index (zz, xz, yz) at zero
-    const float kz = p.dims == 2 ? 0.0f : keep;
+    const bool flat = p.dims == 2;
+    const float kz = flat ? 0.0f : keep;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) st[(1 + a) * N + n] = S::store((a == 2 ? kz : keep) * u[a * N + n], p.scale[1]);
+    for (int a = 0; a < 3; ++a)
+        put(1 + a, (a == 2 ? kz : keep) * u[a * N + n], p.scale[1], wall || (flat && a == 2));
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-        const float kk = (k == 2 || k == 4 || k == 5) ? kz : keep;
-        st[(4 + k) * N + n] = S::store(pi ? kk * pi[k * N + n] : 0.0f, p.scale[2]);
+        const bool has_z = k == 2 || k == 4 || k == 5;
+        put(4 + k, pi ? (has_z ? kz : keep) * pi[k * N + n] : 0.0f, p.scale[2], wall || (flat && has_z));
     }
 }
 
@@ -438,13 +453,13 @@ hipError_t launch_ghost_fill(int storage, void* st, const StepParams& p, const I
 }
 
 hipError_t launch_pack(int storage, const float* rho, const float* u, const float* pi, int rho_dev, void* st,
-                       const StepParams& p, hipStream_t s) {
+                       void* other, const StepParams& p, hipStream_t s) {
     const int block = 256;
     const unsigned grid = (unsigned)((p.geo.N + block - 1) / block);
     switch (storage) {
-    case 0: hipLaunchKernelGGL(pack_kernel<StoreF32>, dim3(grid), dim3(block), 0, s, rho, u, pi, rho_dev, (float*)st, p); break;
-    case 1: hipLaunchKernelGGL(pack_kernel<StoreF16>, dim3(grid), dim3(block), 0, s, rho, u, pi, rho_dev, (__half*)st, p); break;
-    case 2: hipLaunchKernelGGL(pack_kernel<StoreBF16>, dim3(grid), dim3(block), 0, s, rho, u, pi, rho_dev, (uint16_t*)st, p); break;
+    case 0: hipLaunchKernelGGL(pack_kernel<StoreF32>, dim3(grid), dim3(block), 0, s, rho, u, pi, rho_dev, (float*)st, (float*)other, p); break;
+    case 1: hipLaunchKernelGGL(pack_kernel<StoreF16>, dim3(grid), dim3(block), 0, s, rho, u, pi, rho_dev, (__half*)st, (__half*)other, p); break;
+    case 2: hipLaunchKernelGGL(pack_kernel<StoreBF16>, dim3(grid), dim3(block), 0, s, rho, u, pi, rho_dev, (uint16_t*)st, (uint16_t*)other, p); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -529,6 +544,47 @@ hipError_t launch_stream_copy(const void* src, void* dst, long long n4, hipStrea
     const long long blocks = (n4 + 1023) / 1024;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(stream_copy_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const float4*)src, (float4*)dst, n4);
+    return hipGetLastError();
+}
+
+// State copies: 16-byte words, then the 4-byte tail of a state whose size is
+// no multiple of 16.  Up to 32 MB plain (the copy is read again from the
+// caches: a 10.5 MB state takes 5 us where the runtime's copy took 18),
+// non-temporal beyond.
+template <bool NT>
+__global__ void __launch_bounds__(256) copy_state_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst,
+                                                         long long n4, int tail) {
+    using V = unsigned __attribute__((ext_vector_type(4)));
+    const V* s = reinterpret_cast<const V*>(src);
+    V* d = reinterpret_cast<V*>(dst);
+    const long long base = (long long)blockIdx.x * 1024 + threadIdx.x;
+    V v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (base + 256 * k < n4) v[k] = NT ? __builtin_nontemporal_load(s + base + 256 * k) : s[base + 256 * k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (base + 256 * k < n4) {
+            if constexpr (NT)
+                __builtin_nontemporal_store(v[k], d + base + 256 * k);
+            else
+                d[base + 256 * k] = v[k];
+        }
+    }
+    if (blockIdx.x == 0 && (int)threadIdx.x < tail)
+        reinterpret_cast<unsigned*>(dst + n4)[threadIdx.x] = reinterpret_cast<const unsigned*>(src + n4)[threadIdx.x];
+}
+
+hipError_t launch_copy_state(void* dst, const void* src, size_t bytes, hipStream_t s) {
+    if (bytes == 0) return hipSuccess;
+    const long long n4 = (long long)(bytes / 16), blocks = std::max(1LL, (n4 + 1023) / 1024);
+    if (bytes % 4 != 0 || (((uintptr_t)dst | (uintptr_t)src) & 15) != 0 || blocks > 0x7fffffffLL)
+        return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s);
+    const int tail = (int)(bytes % 16 / 4);
+    if (bytes > (32u << 20))
+        hipLaunchKernelGGL(copy_state_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, (const uint4*)src, (uint4*)dst, n4, tail);
+    else
+        hipLaunchKernelGGL(copy_state_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, (const uint4*)src, (uint4*)dst, n4, tail);
     return hipGetLastError();
 }
 

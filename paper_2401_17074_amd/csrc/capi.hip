@@ -280,11 +280,9 @@ int tslb_set_moments(tslb_handle h, const float* rho, const float* u, const floa
         pi = pineq ? h->staging + 4 * N : nullptr;
     }
     void* cur = h->buf[h->cur];
-    HIP_TRY(launch_pack(h->storage, r, v, pi, (flags & TSLB_RHO_DEVIATION) ? 1 : 0, cur, h->p, s));
+    HIP_TRY(launch_pack(h->storage, r, v, pi, (flags & TSLB_RHO_DEVIATION) ? 1 : 0, cur, h->buf[1 - h->cur], h->p, s));
     int rc = fill_ghosts(h, cur, s);
     if (rc) return rc;
-    // keep solid nodes identical in both buffers (the update never writes them)
-    HIP_TRY(hipMemcpyAsync(h->buf[1 - h->cur], cur, h->elem_bytes * 10 * N, hipMemcpyDeviceToDevice, s));
     if (!(flags & TSLB_DEVICE)) HIP_TRY(hipStreamSynchronize(s));
     return TSLB_OK;
 }
@@ -627,7 +625,9 @@ int tslb_load_state(tslb_handle h, const void* src, void* stream) {
     if (!h || !src) return fail(TSLB_E_INVALID, "NULL handle or source");
     DeviceGuard dg(h->device);
     HIP_TRY(hipMemcpyAsync(h->buf[h->cur], src, tslb_state_bytes(h), hipMemcpyDeviceToDevice, S(stream)));
-    HIP_TRY(hipMemcpyAsync(h->buf[1 - h->cur], src, tslb_state_bytes(h), hipMemcpyDeviceToDevice, S(stream)));
+    // the other buffer takes what no step writes: wall nodes, z components
+    if ((h->p.geo.lo_solid | h->p.geo.hi_solid) != 0 || h->p.dims == 2)
+        HIP_TRY(launch_copy_state(h->buf[1 - h->cur], h->buf[h->cur], tslb_state_bytes(h), S(stream)));
     return TSLB_OK;
 }
 
@@ -672,12 +672,12 @@ int tslb_rollout_forward(tslb_handle h, int nsteps, int every, void* ws, size_t 
     if (ws_bytes < tslb_rollout_workspace_bytes(h, nsteps, every)) return fail(TSLB_E_INVALID, "workspace too small");
     if (h->p.order != 3 || h->lattice != TSLB_D3Q27)
         return fail(TSLB_E_UNSUPPORTED, "the adjoint differentiates the third-order D3Q27 update only");
+    DeviceGuard dg(h->device);
     const size_t sb = tslb_state_bytes(h);
     char* ck = (char*)ws;
     for (int s0 = 0, seg = 0; s0 < nsteps; s0 += every, ++seg) {
-        int rc = tslb_save_state(h, ck + (size_t)seg * sb, stream);
-        if (rc) return rc;
-        rc = tslb_step(h, (nsteps - s0 < every) ? nsteps - s0 : every, stream);
+        HIP_TRY(launch_copy_state(ck + (size_t)seg * sb, h->buf[h->cur], sb, S(stream)));
+        const int rc = tslb_step(h, (nsteps - s0 < every) ? nsteps - s0 : every, stream);
         if (rc) return rc;
     }
     return TSLB_OK;
@@ -706,18 +706,19 @@ int tslb_rollout_backward(tslb_handle h, int nsteps, int every, void* ws, size_t
     // nodes are at rest as well.
     if ((h->p.geo.lo_solid | h->p.geo.hi_solid) != 0)
         for (int k = 1; k <= every; ++k)
-            HIP_TRY(hipMemcpyAsync(seg_states + (size_t)k * sb, ck, sb, hipMemcpyDeviceToDevice, s));
+            HIP_TRY(launch_copy_state(seg_states + (size_t)k * sb, ck, sb, s));
     for (int seg = nseg - 1; seg >= 0; --seg) {
         const int s0 = seg * every;
         const int len = (nsteps - s0 < every) ? nsteps - s0 : every;
-        // recompute the segment once from its checkpoint, each level straight
-        // into its slot (the handle's own buffers are not touched)
-        HIP_TRY(hipMemcpyAsync(seg_states, ck + (size_t)seg * sb, sb, hipMemcpyDeviceToDevice, s));
+        // recompute the segment once from its checkpoint (its level 0), each
+        // level straight into its slot (the handle's own buffers are not
+        // touched)
+        auto level = [&](int k) { return k == 0 ? ck + (size_t)seg * sb : seg_states + (size_t)k * sb; };
         for (int k = 1; k <= len; ++k) {
             h->t = t_end - nsteps + s0 + k - 1;
-            HIP_TRY(run_update(h, seg_states + (size_t)(k - 1) * sb, seg_states + (size_t)k * sb, s));
+            HIP_TRY(run_update(h, level(k - 1), level(k), s));
             h->t += 1;
-            const int rc = fill_ghosts(h, seg_states + (size_t)k * sb, s, true);
+            const int rc = fill_ghosts(h, level(k), s, true);
             if (rc) {
                 h->t = t_end;
                 return rc;
@@ -725,8 +726,7 @@ int tslb_rollout_backward(tslb_handle h, int nsteps, int every, void* ws, size_t
         }
         h->t = t_end;
         for (int k = len - 1; k >= 0; --k) {
-            const int rc = tslb_adjoint_step(h, seg_states + (size_t)k * sb, seg_states + (size_t)(k + 1) * sb, a, b,
-                                   dg_accum, stream);
+            const int rc = tslb_adjoint_step(h, level(k), level(k + 1), a, b, dg_accum, stream);
             if (rc) return rc;
             float* tmp = a;
             a = b;
@@ -735,7 +735,7 @@ int tslb_rollout_backward(tslb_handle h, int nsteps, int every, void* ws, size_t
     }
     // the initial level's ghosts were refilled from its interior as well
     if (h->has_ghosts) HIP_TRY(launch_ghost_fold(a, h->p, h->inlet, s));
-    if (a != lam) HIP_TRY(hipMemcpyAsync(lam, a, sizeof(float) * 10 * (size_t)h->p.geo.N, hipMemcpyDeviceToDevice, s));
+    if (a != lam) HIP_TRY(launch_copy_state(lam, a, sizeof(float) * 10 * (size_t)h->p.geo.N, s));
     return TSLB_OK;
 }
 

@@ -41,8 +41,12 @@ hipError_t launch_ghost_fill(int storage, void* st, const StepParams& p, const I
 // Does launch_update_tiled write those x-face ghost nodes for this grid and
 // storage (rows of whole cache lines, no walls, no force field)?
 bool tiled_writes_x_ghosts(int storage, const StepParams& p);
+// other: the second state buffer, which gets what no step writes (wall nodes,
+// the z components of a two-dimensional lattice)
 hipError_t launch_pack(int storage, const float* rho, const float* u, const float* pi, int rho_dev, void* st,
-                       const StepParams& p, hipStream_t s);
+                       void* other, const StepParams& p, hipStream_t s);
+// Device-to-device copy; src and dst do not overlap.
+hipError_t launch_copy_state(void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t launch_unpack(int storage, const void* st, float* rho, float* u, float* pi, int rho_dev,
                          const StepParams& p, hipStream_t s);
 // FP64 sums over fluid nodes, in a fixed order: mass, momentum (3), kinetic
