@@ -120,39 +120,14 @@ struct Fields2 {
     const float* g[2];
 };
 
-// One node's stored values as they come from memory, and its force.
-template <class T>
-struct Raw2 {
-    T m[6];
-    float g[2];
-};
-
-template <bool FIELD, class T>
-__device__ __forceinline__ void fetch2(const Fields2<T>& f, unsigned off, Raw2<T>& r) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) r.m[k] = *(const T*)((const char*)f.in[k] + off);
-    if constexpr (FIELD) {
-        r.g[0] = *(const float*)((const char*)f.g[0] + (off / sizeof(T)) * 4u);
-        r.g[1] = *(const float*)((const char*)f.g[1] + (off / sizeof(T)) * 4u);
-    }
-}
-
 template <class S>
-__device__ __forceinline__ void decode2(const Raw2<typename S::T>& r, const StepParams& p, float m[6]) {
-    m[0] = S::load(r.m[0], p.inv_scale[0]);
+__device__ __forceinline__ void load6(const Fields2<typename S::T>& f, unsigned off, const StepParams& p, float m[6]) {
+    using T = typename S::T;
+    m[0] = S::load(*(const T*)((const char*)f.in[0] + off), p.inv_scale[0]);
 #pragma unroll
-    for (int k = 1; k < 3; ++k) m[k] = S::load(r.m[k], p.inv_scale[1]);
+    for (int k = 1; k < 3; ++k) m[k] = S::load(*(const T*)((const char*)f.in[k] + off), p.inv_scale[1]);
 #pragma unroll
-    for (int k = 3; k < 6; ++k) m[k] = S::load(r.m[k], p.inv_scale[2]);
-}
-
-// The loaded values are needed from here on: the wait for them stands here,
-// ahead of the stores that follow.
-template <bool FIELD, class T>
-__device__ __forceinline__ void arrive2(Raw2<T>& r) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(r.m[k]));
-    if constexpr (FIELD) asm volatile("" : "+v"(r.g[0]), "+v"(r.g[1]));
+    for (int k = 3; k < 6; ++k) m[k] = S::load(*(const T*)((const char*)f.in[k] + off), p.inv_scale[2]);
 }
 
 __device__ __forceinline__ int wrap_clamp(int v, int n, bool periodic) {
@@ -189,7 +164,7 @@ __global__ void __launch_bounds__(kD2Block) update_d2q9_kernel(const Fields2<typ
     // lanes read are mostly hits.
     const int per = (int)(gridDim.x >> 3);
     const int vb = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    const int item = vb * (kD2Block / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int item = vb * (kD2Block / 64) + (int)(threadIdx.x >> 6);
     if (item >= strips * segments) return;  // whole wavefronts leave together
     const int strip = item % strips, seg = item / strips;
     const int y0 = seg * seg_rows, y1 = min(y0 + seg_rows, ny);
@@ -223,34 +198,34 @@ __global__ void __launch_bounds__(kD2Block) update_d2q9_kernel(const Fields2<typ
         return lane == kStrip - 1 ? h : w;
     };
 
-    Raw2<T> own, side;  // row yp on entry to row(yp); side: the edge lanes' neighbour
-#pragma unroll
-    for (int k = 0; k < 6; ++k) side.m[k] = T{};
-    side.g[0] = side.g[1] = 0.0f;
-    auto fetch = [&](int yp) {
-        const unsigned r = (unsigned)(nx * wrap_clamp(yp, ny, py));  // byte offsets < 2^32: N < 2^30
-        if (edge) fetch2<FIELD>(f, ((unsigned)hx + r) * (unsigned)sizeof(T), side);
-        fetch2<FIELD>(f, ((unsigned)x + r) * (unsigned)sizeof(T), own);
-    };
     auto row = [&](int yp, Sums2& aprev, Sums2& acur, Sums2& anext) {
         const int y = wrap_clamp(yp, ny, py);
+        const unsigned off = (unsigned)(x + nx * y) * (unsigned)sizeof(T);  // < 2^32: N < 2^30
         float m[6];
-        decode2<S>(own, p, m);
-        const bool row_solid = (y == 0 && (g.lo_solid & 2)) || (y == ny - 1 && (g.hi_solid & 2));
-        const bool solid = col_solid || row_solid;
-        const float gxv = solid ? 0.0f : FIELD ? own.g[0] : p.force[0];
-        const float gyv = solid ? 0.0f : FIELD ? own.g[1] : p.force[1];
+        load6<S>(f, off, p, m);
+        const bool solid = col_solid || (y == 0 && (g.lo_solid & 2)) || (y == ny - 1 && (g.hi_solid & 2));
+        float gxv = 0.0f, gyv = 0.0f;
+        if (!solid) {
+            gxv = FIELD ? *(const float*)((const char*)f.g[0] + (off / sizeof(T)) * 4u) : p.force[0];
+            gyv = FIELD ? *(const float*)((const char*)f.g[1] + (off / sizeof(T)) * 4u) : p.force[1];
+        }
         float b[8];
         coefficients2<ORDER>(m, gxv, gyv, omo, b);
+        float G[9];
+        populations2(b, G);
         // halo populations H[cy + 1] = 36 w P(hs, cy) of node (hx, y), with
         // P(s, cy) = r0 + cy r1 + cy^2 r2 and 36 w = 4^(cy == 0)
         float H[3] = {0.0f, 0.0f, 0.0f};
         if (edge) {
             float mh[6], bh[8];
-            decode2<S>(side, p, mh);
-            const bool hsolid = hsolid_col || row_solid;
-            const float hgx = hsolid ? 0.0f : FIELD ? side.g[0] : p.force[0];
-            const float hgy = hsolid ? 0.0f : FIELD ? side.g[1] : p.force[1];
+            const unsigned hoff = (unsigned)(hx + nx * y) * (unsigned)sizeof(T);
+            load6<S>(f, hoff, p, mh);
+            const bool hsolid = hsolid_col || (y == 0 && (g.lo_solid & 2)) || (y == ny - 1 && (g.hi_solid & 2));
+            float hgx = 0.0f, hgy = 0.0f;
+            if (!hsolid) {
+                hgx = FIELD ? *(const float*)((const char*)f.g[0] + (hoff / sizeof(T)) * 4u) : p.force[0];
+                hgy = FIELD ? *(const float*)((const char*)f.g[1] + (hoff / sizeof(T)) * 4u) : p.force[1];
+            }
             coefficients2<ORDER>(mh, hgx, hgy, omo, bh);
             const float r0 = bh[0] + hs * bh[1] + bh[3], r1 = bh[2] + hs * bh[5] + bh[6], r2 = bh[4] + hs * bh[7];
             const float t2 = r0 + r2;
@@ -258,10 +233,6 @@ __global__ void __launch_bounds__(kD2Block) update_d2q9_kernel(const Fields2<typ
             H[1] = 4.0f * r0;
             H[2] = t2 + r1;
         }
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(min(yp + 1, y1));  // past the last row: that row again, not used
-        float G[9];
-        populations2(b, G);
         // slice c_y = -1 (I = 0, 1, 2) arrives in row yp - 1
         aprev.template add<-1, -1>(from_right(G[0], H[0]));
         aprev.template add<0, -1>(G[1]);
@@ -294,6 +265,8 @@ __global__ void __launch_bounds__(kD2Block) update_d2q9_kernel(const Fields2<typ
         }
 
         const int yo = yp - 1;  // row yp - 1 is complete
+        if (!(fluid_col && yo >= y0 && yo < y1)) return;
+        if ((yo == 0 && ((g.lo_solid | g.lo_ghost) & 2)) || (yo == ny - 1 && ((g.hi_solid | g.hi_ghost) & 2))) return;
         const Sums2& a = aprev;
         // drho' = D/36, u' = J/(36 + D), Pi' = (S - J u' - D/3 delta)/36
         const float den = 36.0f + a.d;
@@ -301,27 +274,18 @@ __global__ void __launch_bounds__(kD2Block) update_d2q9_kernel(const Fields2<typ
         inv = inv * fmaf(-den, inv, 2.0f);
         const float ux = a.jx * inv, uy = a.jy * inv, d3 = a.d * (1.0f / 3.0f);
         constexpr float k36 = 1.0f / 36.0f;
-        const T o[6] = {S::store(a.d * k36, p.scale[0]),
-                        S::store(ux, p.scale[1]),
-                        S::store(uy, p.scale[1]),
-                        S::store((a.sxx - a.jx * ux - d3) * k36, p.scale[2]),
-                        S::store((a.syy - a.jy * uy - d3) * k36, p.scale[2]),
-                        S::store((a.sxy - a.jx * uy) * k36, p.scale[2])};
-        __builtin_amdgcn_sched_barrier(0);
-        arrive2<FIELD>(own);
-        arrive2<FIELD>(side);
-        __builtin_amdgcn_sched_barrier(0);
-        if (!(fluid_col && yo >= y0 && yo < y1)) return;
-        if ((yo == 0 && ((g.lo_solid | g.lo_ghost) & 2)) || (yo == ny - 1 && ((g.hi_solid | g.hi_ghost) & 2))) return;
         const unsigned oo = (unsigned)(x + nx * yo) * (unsigned)sizeof(T);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) out_store<NT>((T*)((char*)f.out[k] + oo), o[k]);
+        out_store<NT>((T*)((char*)f.out[0] + oo), S::store(a.d * k36, p.scale[0]));
+        out_store<NT>((T*)((char*)f.out[1] + oo), S::store(ux, p.scale[1]));
+        out_store<NT>((T*)((char*)f.out[2] + oo), S::store(uy, p.scale[1]));
+        out_store<NT>((T*)((char*)f.out[3] + oo), S::store((a.sxx - a.jx * ux - d3) * k36, p.scale[2]));
+        out_store<NT>((T*)((char*)f.out[4] + oo), S::store((a.syy - a.jy * uy - d3) * k36, p.scale[2]));
+        out_store<NT>((T*)((char*)f.out[5] + oo), S::store((a.sxy - a.jx * uy) * k36, p.scale[2]));
     };
 
     Sums2 a0, a1, a2;
     a0.zero();
     a1.zero();
-    fetch(y0 - 1);
     for (int yp = y0 - 1; yp <= y1; yp += 3) {
         row(yp, a0, a1, a2);
         if (yp + 1 > y1) break;
