@@ -79,7 +79,7 @@ def test_bricks(kind, nx, xface):
     _check(kind, nx, 13, 5, xface)
 
 
-# tiles of 64 x 12, 37 rows one past a tile, segments of one and two planes
+# tiles of 64 x 12 (FP32) or 64 x 13, 37 rows one past a tile of 12, segments of one and two planes
 @pytest.mark.parametrize("kind", [0, 1, 2])
 @pytest.mark.parametrize("nx", [63, 64, 65, 130])
 @pytest.mark.parametrize("xface", [P, X, O])
@@ -115,3 +115,47 @@ def test_other_lattice_and_order(lattice, order, dims):
     u, u2 = np.abs(want[1:4][:, fl]).max(), (want[1:4][:, fl] ** 2).sum(axis=0).max()
     size = [max(np.abs(want[0][fl] - 1.0).max(), u)] + [u] * 3 + [max(np.abs(want[4:][:, fl]).max(), u2)] * 6
     assert np.all(np.abs(got - want)[:, fl] <= 16 * EPS32 * np.array(size)[:, None])
+
+
+# tiles of 64 x 13 (16-bit storage): 40 rows one past a tile
+@pytest.mark.parametrize("kind", [1, 2])
+@pytest.mark.parametrize("xface", [P, X, O])
+def test_thirteen_row_tiles(kind, xface):
+    _check(kind, 65, 40, 101, xface)
+
+
+@pytest.mark.parametrize("field", [False, True])
+@pytest.mark.parametrize("dims", [(1, 13, 5), (63, 12, 9), (64, 25, 4), (130, 37, 101), (66, 70, 203)])
+@pytest.mark.parametrize("xface", [P, X, O])
+def test_adjoint(dims, field, xface):
+    """One adjoint step where tiles, segments and roles meet an edge, with and
+    without a force field and its gradient.  Every result is a sum of at most
+    a few hundred products of values of the same size: 64 binary32 ulps of
+    the largest."""
+    import torch
+    if xface != P and min(dims) < 3:
+        pytest.skip("a non-periodic axis needs 3 nodes")
+    faces = {P: (P,) * 6, X: (X, X, X, X, P, P), O: (O, O, P, P, O, O)}[xface]
+    case = W.Case("adj", *dims, 0.62, faces=faces, force=(2e-6, 1e-6, 0.0))
+    G = oracle_grid(case)
+    st0 = W.random_state(case.shape, seed=51, u_amp=0.05, pi_amp=2e-3)
+    st0 = W.to_fp32(oracle.ghost_fill(G, st0, 0) if xface == O else st0)
+    g = W.random_force(case.shape, seed=52, amp=1e-4).astype(np.float32).astype(np.float64) if field else None
+    lam1 = np.random.default_rng(53).standard_normal(st0.shape).astype(np.float32).astype(np.float64)
+    if xface != O:
+        lam1[:, oracle.node_kinds(G) != 0] = 0.0
+    s = gpu_solver(case)
+    if field:
+        s.set_force_field(g)
+    s.set_state(to_device_state(st0))
+    raw0 = s.save_raw()
+    s.step(1)
+    raw1 = s.save_raw()
+    dg = torch.zeros((3,) + case.shape, dtype=torch.float32, device="cuda") if field else None
+    lam0 = s.adjoint_step(raw0, raw1, torch.tensor(lam1, dtype=torch.float32, device="cuda"), dg)
+    lam0 = lam0.double().cpu().numpy()
+    s.close()
+    want, want_dg = oracle.adjoint_step(G, st0, lam1, g)
+    assert np.abs(lam0 - want).max() <= 64 * EPS32 * np.abs(want).max()
+    if field:
+        assert np.abs(dg.double().cpu().numpy() - want_dg).max() <= 64 * EPS32 * np.abs(want_dg).max()
