@@ -11,6 +11,10 @@
 
 namespace tslb {
 
+// Last-level (Infinity) cache of the card: a step whose two levels fit finds
+// its input there.
+constexpr size_t kInfinityCacheBytes = (size_t)256 << 20;
+
 // Launchers (stream-ordered, no synchronisation).  `storage` selects the
 // stored format (0 FP32, 1 FP16, 2 BF16); buffers are the raw state arrays.
 hipError_t launch_update_direct(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);

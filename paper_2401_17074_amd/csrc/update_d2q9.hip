@@ -7,34 +7,69 @@
 // Pi_xx, Pi_yy, Pi_xy only (u_z and the Pi components with a z index stay
 // zero).
 //
-// Kernel shape: one wavefront owns a strip of 64 x-columns (whole cache
-// lines) and marches a segment of rows along y.  For every row it builds
-// the 9 populations of its 64 nodes (scaled deviations G = 36 w P,
-// 36 w = 4^n0 exact), moves the ones with c_x != 0 to their x-neighbour with
-// a cross-lane permute (no LDS allocation, no block barrier; the two edge
-// lanes rebuild the three values that enter from the neighbouring strips),
-// and adds each c_y slice into the rolling accumulator of the row it arrives
-// in (rows y - 1, y, y + 1).  Row y - 1 is then complete and is
-// finalised and stored.  Walls: wall nodes are stored as the rest state and
-// emit nothing; a fluid node next to a wall adds its own bounced-back
-// populations, straight from the nine it has just built, to its own row
-// (half-way bounce-back).
+// Kernel shape: one wavefront owns a span of 64 or 128 x-columns (one or two
+// per lane, 64 apart, so that every load is whole cache lines) and marches a
+// segment of rows along y.  For every row it builds the 9 populations of its
+// nodes (without their weights, which the sums apply), moves the ones with
+// c_x != 0 to their x-neighbour across lanes (no LDS, no block barrier; the
+// two edge lanes rebuild the three values that enter from the neighbouring
+// spans), and adds each c_y slice to the row it arrives in (rows y - 1, y,
+// y + 1).  Row y - 1 is then complete and is finalised and stored.  Walls:
+// wall nodes are stored as the rest state and emit nothing; a fluid node next
+// to a wall adds its own bounced-back populations, straight from the nine it
+// has just built, to its own row (half-way bounce-back).
+//
+// What bounds it (8192 x 4096 channel): memory with FP32 storage, 320 us (5.0
+// TB/s), arithmetic with FP16, 194 us.  It took 351 and 225 us with one
+// column per lane (the edge lanes' node costs the wave as much as its own),
+// nine values summed one by one, shifts through LDS permutes, a second load
+// round trip for the edge lanes and stores ahead of the next row's loads (a
+// wait for loads waits for the stores before them): now the next row's loads
+// go out once this row's have been used and have arrived before its stores.
+#include <algorithm>
+
 #include "tslb_internal.h"
 
 namespace tslb {
 namespace {
 
-#ifndef TSLB_D2_WAVES
-#define TSLB_D2_WAVES 32
-#endif
 constexpr int kD2Block = 256;          // four independent wavefronts
-constexpr int kStrip = 64;             // columns per wavefront: one per lane, whole cache lines
 
+
+// One c_y slice of arriving deviations (c_x = -1, 0, 1), without lattice
+// weights, reduced along x: sum, sum c_x and sum c_x^2 with the factor 4 of a
+// zero component applied (36 w = 4^n0).
+struct Slice2 {
+    float t, d, s;
+};
+__device__ __forceinline__ Slice2 slice2(float m, float z, float p) {
+    const float s = p + m;
+    return {fmaf(4.0f, z, s), p - m, s};
+}
 
 // Moment sums of the arriving scaled deviations (2D).
 struct Sums2 {
     float d, jx, jy, sxx, syy, sxy;
-    __device__ __forceinline__ void zero() { d = jx = jy = sxx = syy = sxy = 0.0f; }
+    // the slices c_y = +1 (q, the first to reach a row), 0 and -1
+    __device__ __forceinline__ void start(const Slice2& q) {
+        d = jy = syy = q.t;
+        jx = sxy = q.d;
+        sxx = q.s;
+    }
+    __device__ __forceinline__ void middle(const Slice2& q) {
+        d = fmaf(4.0f, q.t, d);
+        jx = fmaf(4.0f, q.d, jx);
+        sxx = fmaf(4.0f, q.s, sxx);
+    }
+    __device__ __forceinline__ void finish(const Slice2& q) {
+        d += q.t;
+        jx += q.d;
+        jy -= q.t;
+        sxx += q.s;
+        syy += q.t;
+        sxy -= q.d;
+    }
+    // one arriving value, weight applied
     template <int CX, int CY>
     __device__ __forceinline__ void add(float f) {
         d += f;
@@ -47,6 +82,9 @@ struct Sums2 {
             syy += f;
         }
         if (CX * CY) sxy += CX * CY * f;
+    }
+    __device__ __forceinline__ void complete() {
+        asm volatile("" : "+v"(d), "+v"(jx), "+v"(jy), "+v"(sxx), "+v"(syy), "+v"(sxy));
     }
 };
 
@@ -86,8 +124,8 @@ __device__ __forceinline__ void coefficients2(const float m[6], float gx, float 
     b[7] = 3.0f * b[4] * ux + qxy * uy;
 }
 
-// G[3 (cy + 1) + (cx + 1)] = 4^n0 P(cx, cy) (36 w = 4^n0, n0 the number of
-// zero components): along x for each power of cy, then along y.
+// G[3 (cy + 1) + (cx + 1)] = P(cx, cy), without the weight: along x for each
+// power of cy, then along y.
 __device__ __forceinline__ void populations2(const float b[8], float G[9]) {
     const float s0 = b[0] + b[3], s1 = b[2] + b[6];
     const float r0[3] = {s0 - b[1], b[0], s0 + b[1]};
@@ -98,15 +136,20 @@ __device__ __forceinline__ void populations2(const float b[8], float G[9]) {
         const float t = r0[ix] + r2[ix];
         const float q[3] = {t - r1[ix], r0[ix], t + r1[ix]};
 #pragma unroll
-        for (int iy = 0; iy < 3; ++iy) {
-            const int n0 = (ix == 1) + (iy == 1);
-            G[3 * iy + ix] = n0 == 0 ? q[iy] : (float)(1 << (2 * n0)) * q[iy];
-        }
+        for (int iy = 0; iy < 3; ++iy) G[3 * iy + ix] = q[iy];
     }
 }
 
-__device__ __forceinline__ float from_lane(int src_lane, float v) {
-    return __int_as_float(__builtin_amdgcn_ds_bpermute(src_lane << 2, __float_as_int(v)));
+// v of the next lane (wave_shr:1 0x138: the lane on the left, wave_shl:1
+// 0x130: on the right); the end lane without one gets h.
+template <int CTRL>
+__device__ __forceinline__ float shift_lane(float v, float h) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(h), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
+// v of one lane, in all of them.
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
 // Per-field base pointers of the six stored D2Q9 fields (drho, u_x, u_y,
@@ -120,14 +163,39 @@ struct Fields2 {
     const float* g[2];
 };
 
+// One node's stored values as they come from memory, and its force.
+template <class T>
+struct Raw2 {
+    T m[6];
+    float g[2];
+};
+
+template <bool FIELD, class T>
+__device__ __forceinline__ void fetch2(const Fields2<T>& f, unsigned off, Raw2<T>& r) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) r.m[k] = *(const T*)((const char*)f.in[k] + off);
+    if constexpr (FIELD) {
+        r.g[0] = *(const float*)((const char*)f.g[0] + (off / sizeof(T)) * 4u);
+        r.g[1] = *(const float*)((const char*)f.g[1] + (off / sizeof(T)) * 4u);
+    }
+}
+
 template <class S>
-__device__ __forceinline__ void load6(const Fields2<typename S::T>& f, unsigned off, const StepParams& p, float m[6]) {
-    using T = typename S::T;
-    m[0] = S::load(*(const T*)((const char*)f.in[0] + off), p.inv_scale[0]);
+__device__ __forceinline__ void decode2(const Raw2<typename S::T>& r, const StepParams& p, float m[6]) {
+    m[0] = S::load(r.m[0], p.inv_scale[0]);
 #pragma unroll
-    for (int k = 1; k < 3; ++k) m[k] = S::load(*(const T*)((const char*)f.in[k] + off), p.inv_scale[1]);
+    for (int k = 1; k < 3; ++k) m[k] = S::load(r.m[k], p.inv_scale[1]);
 #pragma unroll
-    for (int k = 3; k < 6; ++k) m[k] = S::load(*(const T*)((const char*)f.in[k] + off), p.inv_scale[2]);
+    for (int k = 3; k < 6; ++k) m[k] = S::load(r.m[k], p.inv_scale[2]);
+}
+
+// The loaded values are needed from here on: the wait for them stands here,
+// ahead of the stores that follow.
+template <bool FIELD, class T>
+__device__ __forceinline__ void arrive2(Raw2<T>& r) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(r.m[k]));
+    if constexpr (FIELD) asm volatile("" : "+v"(r.g[0]), "+v"(r.g[1]));
 }
 
 __device__ __forceinline__ int wrap_clamp(int v, int n, bool periodic) {
@@ -138,9 +206,7 @@ __device__ __forceinline__ int wrap_clamp(int v, int n, bool periodic) {
     return v < 0 ? 0 : (v >= n ? n - 1 : v);
 }
 
-// Output stores, non-temporal (the new level is not read again by this
-// launch) when every grid row is a whole number of 128-B cache lines, plain
-// otherwise (a strip's row then straddles lines its neighbour completes).
+// Output stores, non-temporal or plain (see launch_o).
 template <bool NT, class T>
 __device__ __forceinline__ void out_store(T* p, T v) {
     if constexpr (!NT)
@@ -151,157 +217,197 @@ __device__ __forceinline__ void out_store(T* p, T v) {
         __builtin_nontemporal_store(__builtin_bit_cast(unsigned short, v), reinterpret_cast<unsigned short*>(p));
 }
 
-template <class S, int ORDER, bool FIELD, bool NT>
-__global__ void __launch_bounds__(kD2Block) update_d2q9_kernel(const Fields2<typename S::T> f, StepParams p, int strips,
+template <class S, int ORDER, bool FIELD, bool NT, int C>
+__global__ void __launch_bounds__(kD2Block) update_d2q9_kernel(const Fields2<typename S::T> f, StepParams p, int spans,
                                                                int segments, int seg_rows) {
     using T = typename S::T;
     const Geometry& g = p.geo;
     const int nx = g.n[0], ny = g.n[1];
     const int lane = threadIdx.x & 63;
     // Block ids are dealt round-robin to the 8 XCDs (the grid is a multiple
-    // of 8 blocks); each XCD takes a contiguous run of blocks, so the strips
+    // of 8 blocks); each XCD takes a contiguous run of blocks, so the spans
     // that march side by side share an L2 and the halo columns the edge
     // lanes read are mostly hits.
     const int per = (int)(gridDim.x >> 3);
     const int vb = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    const int item = vb * (kD2Block / 64) + (int)(threadIdx.x >> 6);
-    if (item >= strips * segments) return;  // whole wavefronts leave together
-    const int strip = item % strips, seg = item / strips;
+    const int item = vb * (kD2Block / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (item >= spans * segments) return;  // whole wavefronts leave together
+    const int span = item % spans, seg = item / spans;
     const int y0 = seg * seg_rows, y1 = min(y0 + seg_rows, ny);
-    const int x0 = strip * kStrip, gx = x0 + lane;
+    const int x0 = span * (64 * C);
     const bool px = (g.periodic & 1) != 0, py = (g.periodic & 2) != 0;
-    // lanes past the last column build the node the periodic wrap or the
-    // clamp puts there (its populations still reach the last column)
-    const int x = wrap_clamp(gx, nx, px);
-    const bool interior = gx < nx;
-    // the edge lanes also rebuild the populations that enter the strip from
+    // The edge lanes also rebuild the populations that enter the span from
     // the neighbouring columns: lane 0 those with c_x = +1 of node x0 - 1,
-    // lane 63 those with c_x = -1 of node x0 + 64
-    const bool edge = lane == 0 || lane == kStrip - 1;
-    const int hx = wrap_clamp(lane == 0 ? x0 - 1 : x0 + kStrip, nx, px);
+    // lane 63 those with c_x = -1 of node x0 + 64 C.
+    const bool edge = lane == 0 || lane == 63;
+    const int hx = wrap_clamp(lane == 0 ? x0 - 1 : x0 + 64 * C, nx, px);
     const float hs = lane == 0 ? 1.0f : -1.0f;
-    const bool hsolid_col = (hx == 0 && (g.lo_solid & 1)) || (hx == nx - 1 && (g.hi_solid & 1));
-    const bool col_solid = (x == 0 && (g.lo_solid & 1)) || (x == nx - 1 && (g.hi_solid & 1));
-    const bool fluid_col = interior && !col_solid && !(x == 0 && (g.lo_ghost & 1)) && !(x == nx - 1 && (g.hi_ghost & 1));
-    const bool wl = (g.lo_solid & 1) && x == 1, wr = (g.hi_solid & 1) && x == nx - 2;
+    auto solid_at = [&](int x) { return (x == 0 && (g.lo_solid & 1)) || (x == nx - 1 && (g.hi_solid & 1)); };
+    const bool hsolid_col = solid_at(hx);
+    int x[C];  // lanes past the last column build the node the periodic wrap or the
+               // clamp puts there (its populations still reach the last column)
+    bool col_solid[C], fluid_col[C], wl[C], wr[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int gx = x0 + 64 * c + lane;
+        x[c] = wrap_clamp(gx, nx, px);
+        col_solid[c] = solid_at(x[c]);
+        fluid_col[c] = gx < nx && !col_solid[c] && !(x[c] == 0 && (g.lo_ghost & 1)) && !(x[c] == nx - 1 && (g.hi_ghost & 1));
+        wl[c] = (g.lo_solid & 1) && x[c] == 1;
+        wr[c] = (g.hi_solid & 1) && x[c] == nx - 2;
+    }
     const float omo = omo_at(p, 0);
-    // arrivals at this lane: the population with c_x = +1 comes from the
-    // lane on the left (lane 0: its halo value), c_x = -1 from the lane on
-    // the right (lane 63: its halo value)
-    const int left = (lane + 63) & 63, right = (lane + 1) & 63;
-    auto from_left = [&](float v, float h) {
-        const float w = from_lane(left, v);
-        return lane == 0 ? h : w;
-    };
-    auto from_right = [&](float v, float h) {
-        const float w = from_lane(right, v);
-        return lane == kStrip - 1 ? h : w;
-    };
 
-    auto row = [&](int yp, Sums2& aprev, Sums2& acur, Sums2& anext) {
+    Raw2<T> own[C], side;  // row yp on entry to row(yp); side: the edge lanes' neighbour
+#pragma unroll
+    for (int k = 0; k < 6; ++k) side.m[k] = T{};
+    side.g[0] = side.g[1] = 0.0f;
+    auto fetch = [&](int yp) {
+        const unsigned r = (unsigned)(nx * wrap_clamp(yp, ny, py));  // byte offsets < 2^32: N < 2^30
+        if (edge) fetch2<FIELD>(f, ((unsigned)hx + r) * (unsigned)sizeof(T), side);
+#pragma unroll
+        for (int c = 0; c < C; ++c) fetch2<FIELD>(f, ((unsigned)x[c] + r) * (unsigned)sizeof(T), own[c]);
+    };
+    // prev: row yp - 1 with two of its slices; fresh: the slice c_y = +1 of row yp
+    Sums2 prev[C];
+    Slice2 fresh[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        fresh[c] = {0.0f, 0.0f, 0.0f};
+        prev[c].start(fresh[c]);
+    }
+    fetch(y0 - 1);
+    for (int yp = y0 - 1; yp <= y1; ++yp) {
         const int y = wrap_clamp(yp, ny, py);
-        const unsigned off = (unsigned)(x + nx * y) * (unsigned)sizeof(T);  // < 2^32: N < 2^30
-        float m[6];
-        load6<S>(f, off, p, m);
-        const bool solid = col_solid || (y == 0 && (g.lo_solid & 2)) || (y == ny - 1 && (g.hi_solid & 2));
-        float gxv = 0.0f, gyv = 0.0f;
-        if (!solid) {
-            gxv = FIELD ? *(const float*)((const char*)f.g[0] + (off / sizeof(T)) * 4u) : p.force[0];
-            gyv = FIELD ? *(const float*)((const char*)f.g[1] + (off / sizeof(T)) * 4u) : p.force[1];
-        }
-        float b[8];
-        coefficients2<ORDER>(m, gxv, gyv, omo, b);
-        float G[9];
-        populations2(b, G);
-        // halo populations H[cy + 1] = 36 w P(hs, cy) of node (hx, y), with
-        // P(s, cy) = r0 + cy r1 + cy^2 r2 and 36 w = 4^(cy == 0)
+        const bool row_solid = (y == 0 && (g.lo_solid & 2)) || (y == ny - 1 && (g.hi_solid & 2));
+        auto build = [&](const Raw2<T>& r, bool solid, float b[8]) {
+            float m[6];
+            decode2<S>(r, p, m);
+            const float gx = solid ? 0.0f : FIELD ? r.g[0] : p.force[0];
+            const float gy = solid ? 0.0f : FIELD ? r.g[1] : p.force[1];
+            coefficients2<ORDER>(m, gx, gy, omo, b);
+        };
+        // halo values H[cy + 1] = P(hs, cy) of node (hx, y), with
+        // P(s, cy) = r0 + cy r1 + cy^2 r2
         float H[3] = {0.0f, 0.0f, 0.0f};
         if (edge) {
-            float mh[6], bh[8];
-            const unsigned hoff = (unsigned)(hx + nx * y) * (unsigned)sizeof(T);
-            load6<S>(f, hoff, p, mh);
-            const bool hsolid = hsolid_col || (y == 0 && (g.lo_solid & 2)) || (y == ny - 1 && (g.hi_solid & 2));
-            float hgx = 0.0f, hgy = 0.0f;
-            if (!hsolid) {
-                hgx = FIELD ? *(const float*)((const char*)f.g[0] + (hoff / sizeof(T)) * 4u) : p.force[0];
-                hgy = FIELD ? *(const float*)((const char*)f.g[1] + (hoff / sizeof(T)) * 4u) : p.force[1];
-            }
-            coefficients2<ORDER>(mh, hgx, hgy, omo, bh);
-            const float r0 = bh[0] + hs * bh[1] + bh[3], r1 = bh[2] + hs * bh[5] + bh[6], r2 = bh[4] + hs * bh[7];
+            float b[8];
+            build(side, hsolid_col || row_solid, b);
+            const float r0 = b[0] + hs * b[1] + b[3], r1 = b[2] + hs * b[5] + b[6], r2 = b[4] + hs * b[7];
             const float t2 = r0 + r2;
             H[0] = t2 - r1;
-            H[1] = 4.0f * r0;
+            H[1] = r0;
             H[2] = t2 + r1;
         }
-        // slice c_y = -1 (I = 0, 1, 2) arrives in row yp - 1
-        aprev.template add<-1, -1>(from_right(G[0], H[0]));
-        aprev.template add<0, -1>(G[1]);
-        aprev.template add<1, -1>(from_left(G[2], H[0]));
-        // slice c_y = 0 (I = 3, 4, 5) stays in row yp
-        acur.template add<-1, 0>(from_right(G[3], H[1]));
-        acur.template add<0, 0>(G[4]);
-        acur.template add<1, 0>(from_left(G[5], H[1]));
-        // slice c_y = +1 (I = 6, 7, 8) starts row yp + 1
-        anext.zero();
-        anext.template add<-1, 1>(from_right(G[6], H[2]));
-        anext.template add<0, 1>(G[7]);
-        anext.template add<1, 1>(from_left(G[8], H[2]));
-        // half-way bounce-back: a fluid node next to a wall receives its own
-        // population along -c for every c whose upstream node x - c is a
-        // wall; it arrives in the node's own row
-        const bool wb = (g.lo_solid & 2) && yp == 1, wt = (g.hi_solid & 2) && yp == ny - 2;
-        if (fluid_col && !solid && (wl || wr || wb || wt)) {
-#define TSLB_BB(I, X, Y) \
-    if ((X == 1 && wl) || (X == -1 && wr) || (Y == 1 && wb) || (Y == -1 && wt)) acur.template add<X, Y>(G[8 - I]);
-            TSLB_BB(0, -1, -1)
-            TSLB_BB(1, 0, -1)
-            TSLB_BB(2, 1, -1)
-            TSLB_BB(3, -1, 0)
-            TSLB_BB(5, 1, 0)
-            TSLB_BB(6, -1, 1)
-            TSLB_BB(7, 0, 1)
-            TSLB_BB(8, 1, 1)
-#undef TSLB_BB
+        float G[C][9];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            float b[8];
+            build(own[c], col_solid[c] || row_solid, b);
+            populations2(b, G[c]);
         }
-
-        const int yo = yp - 1;  // row yp - 1 is complete
-        if (!(fluid_col && yo >= y0 && yo < y1)) return;
-        if ((yo == 0 && ((g.lo_solid | g.lo_ghost) & 2)) || (yo == ny - 1 && ((g.hi_solid | g.hi_ghost) & 2))) return;
-        const Sums2& a = aprev;
-        // drho' = D/36, u' = J/(36 + D), Pi' = (S - J u' - D/3 delta)/36
-        const float den = 36.0f + a.d;
-        float inv = __builtin_amdgcn_rcpf(den);
-        inv = inv * fmaf(-den, inv, 2.0f);
-        const float ux = a.jx * inv, uy = a.jy * inv, d3 = a.d * (1.0f / 3.0f);
-        constexpr float k36 = 1.0f / 36.0f;
-        const unsigned oo = (unsigned)(x + nx * yo) * (unsigned)sizeof(T);
-        out_store<NT>((T*)((char*)f.out[0] + oo), S::store(a.d * k36, p.scale[0]));
-        out_store<NT>((T*)((char*)f.out[1] + oo), S::store(ux, p.scale[1]));
-        out_store<NT>((T*)((char*)f.out[2] + oo), S::store(uy, p.scale[1]));
-        out_store<NT>((T*)((char*)f.out[3] + oo), S::store((a.sxx - a.jx * ux - d3) * k36, p.scale[2]));
-        out_store<NT>((T*)((char*)f.out[4] + oo), S::store((a.syy - a.jy * uy - d3) * k36, p.scale[2]));
-        out_store<NT>((T*)((char*)f.out[5] + oo), S::store((a.sxy - a.jx * uy) * k36, p.scale[2]));
-    };
-
-    Sums2 a0, a1, a2;
-    a0.zero();
-    a1.zero();
-    for (int yp = y0 - 1; yp <= y1; yp += 3) {
-        row(yp, a0, a1, a2);
-        if (yp + 1 > y1) break;
-        row(yp + 1, a1, a2, a0);
-        if (yp + 2 > y1) break;
-        row(yp + 2, a2, a0, a1);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(min(yp + 1, y1));  // past the last row: that row again, not used
+        const int yo = yp - 1;   // the row this one completes
+        const bool out_row = yo >= y0 && !(yo == 0 && ((g.lo_solid | g.lo_ghost) & 2)) &&
+                             !(yo == ny - 1 && ((g.hi_solid | g.hi_ghost) & 2));
+        T o[C][6];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            // arrivals of slice cy: c_x = +1 from the lane on the left, -1
+            // from the lane on the right, across the column sets through the
+            // lane at their border
+            auto arrive = [&]<int CY>() {
+                constexpr int r = 3 * (CY + 1);
+                const float hl = c == 0 ? H[CY + 1] : lane_value(G[c == 0 ? 0 : c - 1][r + 2], 63);
+                const float hr = c == C - 1 ? H[CY + 1] : lane_value(G[c == C - 1 ? c : c + 1][r], 0);
+                return slice2(shift_lane<0x130>(G[c][r], hr), G[c][r + 1], shift_lane<0x138>(G[c][r + 2], hl));
+            };
+            Sums2 a = prev[c];
+            a.finish(arrive.template operator()<-1>());  // row yp - 1
+            Sums2& cur = prev[c];
+            cur.start(fresh[c]);
+            cur.middle(arrive.template operator()<0>());  // row yp
+            fresh[c] = arrive.template operator()<1>();   // row yp + 1
+            // half-way bounce-back: a fluid node next to a wall receives its
+            // own population along -c for every c whose upstream node x - c
+            // is a wall; it arrives in the node's own row
+            const bool wb = (g.lo_solid & 2) && yp == 1, wt = (g.hi_solid & 2) && yp == ny - 2;
+            if (fluid_col[c] && !row_solid && (wl[c] || wr[c] || wb || wt)) {
+#define TSLB_BB(I, X, Y)                                                                  \
+    if ((X == 1 && wl[c]) || (X == -1 && wr[c]) || (Y == 1 && wb) || (Y == -1 && wt)) \
+        cur.template add<X, Y>(((X == 0) + (Y == 0) == 1 ? 4.0f : 1.0f) * G[c][8 - I]);
+                TSLB_BB(0, -1, -1)
+                TSLB_BB(1, 0, -1)
+                TSLB_BB(2, 1, -1)
+                TSLB_BB(3, -1, 0)
+                TSLB_BB(5, 1, 0)
+                TSLB_BB(6, -1, 1)
+                TSLB_BB(7, 0, 1)
+                TSLB_BB(8, 1, 1)
+#undef TSLB_BB
+            }
+            cur.complete();
+            // drho' = D/36, u' = J/(36 + D), Pi' = (S - J u' - D/3 delta)/36
+            const float den = 36.0f + a.d;
+            float inv = __builtin_amdgcn_rcpf(den);
+            inv = inv * fmaf(-den, inv, 2.0f);
+            const float ux = a.jx * inv, uy = a.jy * inv, d3 = a.d * (1.0f / 3.0f);
+            constexpr float k36 = 1.0f / 36.0f;
+            o[c][0] = S::store(a.d * k36, p.scale[0]);
+            o[c][1] = S::store(ux, p.scale[1]);
+            o[c][2] = S::store(uy, p.scale[1]);
+            o[c][3] = S::store((a.sxx - a.jx * ux - d3) * k36, p.scale[2]);
+            o[c][4] = S::store((a.syy - a.jy * uy - d3) * k36, p.scale[2]);
+            o[c][5] = S::store((a.sxy - a.jx * uy) * k36, p.scale[2]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < C; ++c) arrive2<FIELD>(own[c]);
+        arrive2<FIELD>(side);
+        __builtin_amdgcn_sched_barrier(0);
+        if (!out_row) continue;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (!fluid_col[c]) continue;
+            const unsigned oo = (unsigned)(x[c] + nx * yo) * (unsigned)sizeof(T);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) out_store<NT>((T*)((char*)f.out[k] + oo), o[c][k]);
+        }
     }
 }
 
+// Spans and segments.  The chip takes 4096 wavefronts at 16 per CU; rows per
+// segment so that there are as many, down to one row: at least three rows of
+// loads in a chain (256 x 256: 5.2 us; with segments of 16 rows 18.6).
+// Two columns per lane where that still leaves segments of eight rows (8192 x
+// 4096: 320 us, 343 with one column; 512 x 512 7.0 and 6.8).  FP32, bound by
+// memory, takes up to 32 rows at eight wavefronts per CU instead, for fewer
+// halo rows (4096 x 2048: 82.4 us with 32 rows, 85.2 with 16); 16-bit storage,
+// bound by arithmetic, does not (2048 x 2048 FP16: 28.6 us with 8 rows, 33.0
+// with 16).
+template <class S, int ORDER, bool FIELD, bool NT>
+hipError_t launch_c(const Fields2<typename S::T>& f, const StepParams& p, hipStream_t s) {
+    const int nx = p.geo.n[0], ny = p.geo.n[1];
+    constexpr long long kWaves = 4096;
+    auto rows = [&](int spans) { return (int)std::max(1LL, ((long long)ny * spans + kWaves - 1) / kWaves); };
+    auto run = [&]<int C>(int seg_rows) {
+        const int spans = (nx + 64 * C - 1) / (64 * C), segments = (ny + seg_rows - 1) / seg_rows;
+        const long long waves = (long long)spans * segments;
+        const unsigned blocks = (unsigned)((waves + kD2Block / 64 - 1) / (kD2Block / 64));
+        const unsigned grid = (blocks + 7u) & ~7u;  // a multiple of 8: whole runs per XCD
+        hipLaunchKernelGGL((update_d2q9_kernel<S, ORDER, FIELD, NT, C>), dim3(grid), dim3(kD2Block), 0, s, f, p, spans,
+                           segments, seg_rows);
+        return hipGetLastError();
+    };
+    const int r2 = rows((nx + 127) / 128);
+    if (r2 < 8) return run.template operator()<1>(rows((nx + 63) / 64));
+    return run.template operator()<2>(sizeof(typename S::T) == 4 ? std::max(r2, std::min(32, 2 * r2)) : r2);
+}
+
 template <class S, int ORDER>
-hipError_t launch_o(const void* in, void* out, const StepParams& p, int strips, int segments, int seg_rows,
-                    hipStream_t s) {
+hipError_t launch_o(const void* in, void* out, const StepParams& p, hipStream_t s) {
     using T = typename S::T;
-    const int waves = strips * segments;
-    const unsigned blocks = (unsigned)((waves + kD2Block / 64 - 1) / (kD2Block / 64));
-    const unsigned grid = (blocks + 7u) & ~7u;  // a multiple of 8: whole runs per XCD
     const size_t N = (size_t)p.geo.N;
     Fields2<T> f;
     const int field[6] = {0, 1, 2, 4, 5, 7};
@@ -310,47 +416,29 @@ hipError_t launch_o(const void* in, void* out, const StepParams& p, int strips, 
         f.out[k] = (T*)out + field[k] * N;
     }
     for (int a = 0; a < 2; ++a) f.g[a] = p.gfield ? p.gfield + a * N : nullptr;
-    const bool nt = ((long long)p.geo.n[0] * (long long)sizeof(T)) % 128 == 0;
-    if (p.gfield && nt)
-        hipLaunchKernelGGL((update_d2q9_kernel<S, ORDER, true, true>), dim3(grid), dim3(kD2Block), 0, s, f, p, strips,
-                           segments, seg_rows);
-    else if (p.gfield)
-        hipLaunchKernelGGL((update_d2q9_kernel<S, ORDER, true, false>), dim3(grid), dim3(kD2Block), 0, s, f, p, strips,
-                           segments, seg_rows);
-    else if (nt)
-        hipLaunchKernelGGL((update_d2q9_kernel<S, ORDER, false, true>), dim3(grid), dim3(kD2Block), 0, s, f, p, strips,
-                           segments, seg_rows);
-    else
-        hipLaunchKernelGGL((update_d2q9_kernel<S, ORDER, false, false>), dim3(grid), dim3(kD2Block), 0, s, f, p, strips,
-                           segments, seg_rows);
-    return hipGetLastError();
+    // Non-temporal stores (the new level is not read again by this launch)
+    // when every row is whole cache lines, so that no line is completed by a
+    // neighbour, and the two levels do not fit the Infinity Cache, where the
+    // next step finds them (2048 x 2048, 201 MB: 47.0 us non-temporal, 35.1
+    // plain; 16384 x 1024, 805 MB: 157 and 162).
+    const bool nt = (p.geo.n[0] * sizeof(T)) % 128 == 0 && 12 * N * sizeof(T) > kInfinityCacheBytes;
+    if (p.gfield) return nt ? launch_c<S, ORDER, true, true>(f, p, s) : launch_c<S, ORDER, true, false>(f, p, s);
+    return nt ? launch_c<S, ORDER, false, true>(f, p, s) : launch_c<S, ORDER, false, false>(f, p, s);
 }
 
 template <class S>
-hipError_t launch_s(const void* in, void* out, const StepParams& p, int strips, int segments, int seg_rows,
-                    hipStream_t s) {
-    return p.order == 2 ? launch_o<S, 2>(in, out, p, strips, segments, seg_rows, s)
-                        : launch_o<S, 3>(in, out, p, strips, segments, seg_rows, s);
+hipError_t launch_s(const void* in, void* out, const StepParams& p, hipStream_t s) {
+    return p.order == 2 ? launch_o<S, 2>(in, out, p, s) : launch_o<S, 3>(in, out, p, s);
 }
 
 }  // namespace
 
 hipError_t launch_update_d2q9(int storage, const void* in, void* out, const StepParams& p, hipStream_t s) {
-    const int nx = p.geo.n[0], ny = p.geo.n[1];
     if (p.geo.n[2] != 1 || p.geo.N >= (1LL << 30)) return hipErrorInvalidValue;  // 32-bit byte offsets
-    const int strips = (nx + kStrip - 1) / kStrip;
-    // rows per segment: enough wavefronts to fill the chip (TSLB_D2_WAVES
-    // per CU, at most 8 per SIMD at <= 64 VGPRs) while keeping the two halo
-    // rows of a segment a small overhead
-    const long long target = 256LL * TSLB_D2_WAVES;
-    long long segments = (target + strips - 1) / strips;
-    int seg_rows = (int)((ny + segments - 1) / segments);
-    if (seg_rows < 16) seg_rows = 16;
-    segments = (ny + seg_rows - 1) / seg_rows;
     switch (storage) {
-    case 0: return launch_s<StoreF32>(in, out, p, strips, (int)segments, seg_rows, s);
-    case 1: return launch_s<StoreF16>(in, out, p, strips, (int)segments, seg_rows, s);
-    case 2: return launch_s<StoreBF16>(in, out, p, strips, (int)segments, seg_rows, s);
+    case 0: return launch_s<StoreF32>(in, out, p, s);
+    case 1: return launch_s<StoreF16>(in, out, p, s);
+    case 2: return launch_s<StoreBF16>(in, out, p, s);
     }
     return hipErrorInvalidValue;
 }

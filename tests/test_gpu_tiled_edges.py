@@ -37,13 +37,15 @@ def _stored(G, st, kind, sc):
     return oracle.round_storage(G, st, kind, sc) if kind else st
 
 
-def _check(kind, nx, ny, nz, xface):
+def _check(kind, nx, ny, nz, xface, lattice=27):
     # y walls with x walls, ghosts on z with x ghosts
-    faces = {P: (P,) * 6, X: (X, X, X, X, P, P), O: (O, O, P, P, O, O)}[xface]
-    case = W.Case("edges", nx, ny, nz, 0.61, faces=faces, force=(2e-6, 1e-6, 0.0))
+    faces = {P: (P,) * 6, X: (X, X, X, X, P, P), O: (O, O, P, P, O, O) if lattice == 27 else (O, O, P, P, P, P)}[xface]
+    case = W.Case("edges", nx, ny, nz, 0.61, faces=faces, force=(2e-6, 1e-6, 0.0), lattice=lattice)
     G, sc = oracle_grid(case), SCALES[kind]
     kinds = oracle.node_kinds(G)
     st0 = W.to_fp32(W.random_state(case.shape, seed=41 + nx, u_amp=0.05, pi_amp=2e-3))
+    if lattice == 9:
+        st0[[3, 6, 8, 9]] = 0.0
     st0 = _stored(G, st0, kind, sc)
     st0[:, kinds == 1] = W.rest_state((1,))[:, 0:1]
     s = gpu_solver(case, storage=kind)
@@ -92,6 +94,17 @@ def test_tiles(kind, nx, xface):
 @pytest.mark.parametrize("xface", [P, X, O])
 def test_longer_segments(kind, xface):
     _check(kind, 66, 70, 203, xface)
+
+
+# D2Q9: spans of 64 columns and segments of one row, then spans of 128 columns
+# (two per lane) with segments of 16 rows (FP32) and 8
+@pytest.mark.parametrize("kind", [0, 1, 2])
+@pytest.mark.parametrize("nx,ny", [(1, 7), (3, 5), (63, 4), (64, 33), (65, 9), (128, 12), (129, 14341), (260, 9600)])
+@pytest.mark.parametrize("xface", [P, X, O])
+def test_d2q9_spans(kind, nx, ny, xface):
+    if xface != P and nx < 3:
+        pytest.skip("a non-periodic axis needs 3 nodes")
+    _check(kind, nx, ny, 1, xface, lattice=9)
 
 
 @pytest.mark.parametrize("lattice,order", [(19, 3), (27, 2), (19, 2)])
