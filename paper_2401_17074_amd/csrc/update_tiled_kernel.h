@@ -567,12 +567,28 @@ hipError_t launch_k(const void* in, void* out, const StepParams& p, hipStream_t 
 
 // Non-temporal output stores when every row starts on a cache line (the new
 // level is not read again by this launch); otherwise plain ones, so that L2
-// merges the lines that neighbouring tiles share (see store_out).
+// merges the lines that neighbouring tiles share (see store_out).  Plain ones
+// also where the two FP32 levels fit the Infinity Cache, in which the next
+// step then finds its input (non-temporal / plain: 128^3 channel, 168 MB, 44.9
+// / 34.6 us; 192 x 128 x 128, 252 MB, 63.2 / 53.1; 160^3 channel, 328 MB, 78.5
+// / 78.9).  16-bit levels, bound by arithmetic there, stay non-temporal (128^3
+// FP16 33.4 / 34.4).
+template <class S>
+bool streams_out(const StepParams& p) {
+    constexpr size_t kSize = sizeof(typename S::T);
+    return rows_whole_lines<S>(p) && (kSize == 2 || 20 * kSize * (size_t)p.geo.N > kInfinityCacheBytes);
+}
+
 template <class S, bool WALLS, bool FIELD, int ORDER, int LAT>
 hipError_t launch_t(const void* in, void* out, const StepParams& p, hipStream_t s) {
+    const bool nt = streams_out<S>(p);
     if constexpr (!WALLS && !FIELD)
-        if (writes_x_ghosts<S>(p)) return launch_k<S, false, false, ORDER, LAT, true, true>(in, out, p, s);
-    if (rows_whole_lines<S>(p)) return launch_k<S, WALLS, FIELD, ORDER, LAT, true, false>(in, out, p, s);
+        if (writes_x_ghosts<S>(p)) {
+            if constexpr (sizeof(typename S::T) == 4)
+                if (!nt) return launch_k<S, false, false, ORDER, LAT, false, true>(in, out, p, s);
+            return launch_k<S, false, false, ORDER, LAT, true, true>(in, out, p, s);
+        }
+    if (nt) return launch_k<S, WALLS, FIELD, ORDER, LAT, true, false>(in, out, p, s);
     return launch_k<S, WALLS, FIELD, ORDER, LAT, false, false>(in, out, p, s);
 }
 

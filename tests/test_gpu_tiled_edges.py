@@ -130,6 +130,13 @@ def test_other_lattice_and_order(lattice, order, dims):
     assert np.all(np.abs(got - want)[:, fl] <= 16 * EPS32 * np.array(size)[:, None])
 
 
+# FP32 levels larger than the Infinity Cache (268 MB): non-temporal stores and
+# loads two planes ahead, segments of odd and even length
+@pytest.mark.parametrize("xface", [P, X, O])
+def test_streamed_tiles(xface):
+    _check(0, 64, 130, 413, xface)
+
+
 # tiles of 64 x 13 (16-bit storage): 40 rows one past a tile
 @pytest.mark.parametrize("kind", [1, 2])
 @pytest.mark.parametrize("xface", [P, X, O])
