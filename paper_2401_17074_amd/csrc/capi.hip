@@ -43,7 +43,7 @@ hipError_t run_update(tslb_ctx* h, const void* in, void* out, hipStream_t s) {
     if (h->lattice == TSLB_D2Q9) return launch_update_d2q9(h->storage, in, out, h->p, s);
     switch (h->kernel) {
     case 0:
-        return h->brick ? launch_update_brick(h->storage, in, out, h->p, s)
+        return h->brick ? launch_update_brick(in, out, h->p, s)
                         : launch_update_tiled(h->storage, in, out, h->p, s);
     case 1: return launch_update_direct(h->storage, in, out, h->p, s);
     case 2: return launch_update_poplayout(h->storage, in, out, h->pop, h->p, s);
@@ -195,9 +195,9 @@ int tslb_create(int nx, int ny, int nz, int lattice, float tau, const float forc
     if (lattice != TSLB_D2Q9) {
         // work list of the tiled update for this grid and this GPU
         std::vector<int4> seg;
-        int grid = 0, nseg = 0;
+        int grid = 0, nseg = 0, other_rows = 0;
         long long steps = 0;
-        if (tiled_schedule(h->storage, g, seg, grid, nseg, steps) != hipSuccess) {
+        if (tiled_schedule(h->storage, g, seg, grid, nseg, other_rows, steps) != hipSuccess) {
             tslb_destroy(h);
             return fail(TSLB_E_INVALID, "no work list for the tiled update of this grid");
         }
@@ -212,7 +212,8 @@ int tslb_create(int nx, int ny, int nz, int lattice, float tau, const float forc
         h->p.sched = h->sched;
         h->p.sched_grid = grid;
         h->p.sched_nseg = nseg;
-        h->brick = prefers_brick(g, steps);
+        h->p.sched_other_rows = other_rows;
+        h->brick = prefers_brick(h->storage, g, steps);
     }
     // rest state: drho = 0, u = 0, Pi = 0 in every format is all-zero bits
     if (hipMemset(h->buf[0], 0, bytes) != hipSuccess || hipMemset(h->buf[1], 0, bytes) != hipSuccess ||

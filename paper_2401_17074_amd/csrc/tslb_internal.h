@@ -14,6 +14,7 @@ namespace tslb {
 // Last-level (Infinity) cache of the card: a step whose two levels fit finds
 // its input there.
 constexpr size_t kInfinityCacheBytes = (size_t)256 << 20;
+constexpr size_t kL2Bytes = (size_t)32 << 20;  // 4 MB per XCD
 
 // Launchers (stream-ordered, no synchronisation).  `storage` selects the
 // stored format (0 FP32, 1 FP16, 2 BF16); buffers are the raw state arrays.
@@ -21,12 +22,14 @@ hipError_t launch_update_direct(int storage, const void* in, void* out, const St
 hipError_t launch_update_poplayout(int storage, const void* in, void* out, float* pop, const StepParams& p,
                                    hipStream_t s);
 // Work list of the tiled update for grid g and a storage format (host-side,
-// see tile::Schedule).
-hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, long long& steps);
-// Update of small grids; does it beat the tiled update on grid g, whose work
+// see tile::Schedule), whether its tiles have 8 (FP32) or 13 rows in place of
+// 12, and the plane-steps of its longest block (FP32: with 12 rows).
+hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, int& other_rows,
+                          long long& steps);
+// Update of small FP32 grids; does it beat the tiled update on grid g, whose work
 // list takes `steps` plane-steps?
-bool prefers_brick(const Geometry& g, long long steps);
-hipError_t launch_update_brick(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
+bool prefers_brick(int storage, const Geometry& g, long long steps);
+hipError_t launch_update_brick(const void* in, void* out, const StepParams& p, hipStream_t s);
 hipError_t launch_update_tiled(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
 hipError_t launch_update_d2q9(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
 int stats_blocks_per_plane(const Geometry& g, int axis);

@@ -24,6 +24,7 @@ struct StepParams {
     // sched_nseg entries {tile column, z begin, z end, 0} per block.
     const int4* sched;
     int sched_grid, sched_nseg;
+    int sched_other_rows;  // its tiles have 8 (FP32) or 13 rows in place of 12
 };
 
 // Inflow description for the ghost refill (Section 2.3).

@@ -108,30 +108,31 @@ __host__ __device__ inline void coefficients(const float m[10], const float g[3]
     const float pxx = omo * m[4], pyy = omo * m[5], pzz = omo * m[6];
     const float pxy = omo * m[7], pxz = omo * m[8], pyz = omo * m[9];
     const float rx = rho * ux, ry = rho * uy, rz = rho * uz;
-    const float uxx = ux * ux, uyy = uy * uy, uzz = uz * uz;
-    const float u2 = uxx + uyy + uzz;
-    const float tr = pxx + pyy + pzz;
-    A[K000] = dr - 1.5f * (rho * u2 + tr);
-    A[K200] = 4.5f * (rx * ux + pxx);
-    A[K020] = 4.5f * (ry * uy + pyy);
-    A[K002] = 4.5f * (rz * uz + pzz);
-    A[K110] = 9.0f * (rx * uy + pxy);
-    A[K101] = 9.0f * (rx * uz + pxz);
-    A[K011] = 9.0f * (ry * uz + pyz);
+    // (sums of products fused in the same way in every kernel and role, so
+    // that a node's populations do not depend on who builds them)
+    const float u2 = fmaf(uz, uz, fmaf(ux, ux, uy * uy));
+    const float tr = fmaf(omo, m[6], fmaf(omo, m[4], pyy));
+    A[K000] = fmaf(-1.5f, fmaf(rho, u2, tr), dr);
+    A[K200] = 4.5f * fmaf(rx, ux, pxx);
+    A[K020] = 4.5f * fmaf(ry, uy, pyy);
+    A[K002] = 4.5f * fmaf(rz, uz, pzz);
+    A[K110] = 9.0f * fmaf(rx, uy, pxy);
+    A[K101] = 9.0f * fmaf(rx, uz, pxz);
+    A[K011] = 9.0f * fmaf(ry, uz, pyz);
     if constexpr (ORDER < 3) {
-        A[K100] = 3.0f * (rx + rho * g[0]);
-        A[K010] = 3.0f * (ry + rho * g[1]);
-        A[K001] = 3.0f * (rz + rho * g[2]);
+        A[K100] = 3.0f * fmaf(rho, g[0], rx);
+        A[K010] = 3.0f * fmaf(rho, g[1], ry);
+        A[K001] = 3.0f * fmaf(rho, g[2], rz);
         A[K210] = A[K201] = A[K120] = A[K021] = A[K102] = A[K012] = A[K111] = 0.0f;
         return;
     }
     if constexpr (LAT == 19) {
-        const float axxy = rx * ux * uy + pxx * uy + 2.0f * pxy * ux;
-        const float ayzz = ry * uz * uz + pzz * uy + 2.0f * pyz * uz;
-        const float axzz = rx * uz * uz + pzz * ux + 2.0f * pxz * uz;
-        const float axyy = rx * uy * uy + pyy * ux + 2.0f * pxy * uy;
-        const float ayyz = ry * uy * uz + pyy * uz + 2.0f * pyz * uy;
-        const float axxz = rx * ux * uz + pxx * uz + 2.0f * pxz * ux;
+        const float axxy = fmaf(2.0f * pxy, ux, fmaf(rx * ux, uy, pxx * uy));
+        const float ayzz = fmaf(2.0f * pyz, uz, fmaf(ry * uz, uz, pzz * uy));
+        const float axzz = fmaf(2.0f * pxz, uz, fmaf(rx * uz, uz, pzz * ux));
+        const float axyy = fmaf(2.0f * pxy, uy, fmaf(rx * uy, uy, pyy * ux));
+        const float ayyz = fmaf(2.0f * pyz, uy, fmaf(ry * uy, uz, pyy * uz));
+        const float axxz = fmaf(2.0f * pxz, ux, fmaf(rx * ux, uz, pxx * uz));
         const float ap = axxy + ayzz, am = axxy - ayzz;
         const float bp = axzz + axyy, bm = axzz - axyy;
         const float cp = ayyz + axxz, cm = ayyz - axxz;
@@ -142,9 +143,9 @@ __host__ __device__ inline void coefficients(const float m[10], const float g[3]
         A[K021] = 13.5f * cp + 4.5f * cm;
         A[K201] = 13.5f * cp - 4.5f * cm;
         A[K111] = 0.0f;
-        A[K100] = 3.0f * (rx + rho * g[0]) - 9.0f * bp;
-        A[K010] = 3.0f * (ry + rho * g[1]) - 9.0f * ap;
-        A[K001] = 3.0f * (rz + rho * g[2]) - 9.0f * cp;
+        A[K100] = fmaf(3.0f, fmaf(rho, g[0], rx), -9.0f * bp);
+        A[K010] = fmaf(3.0f, fmaf(rho, g[1], ry), -9.0f * ap);
+        A[K001] = fmaf(3.0f, fmaf(rho, g[2], rz), -9.0f * cp);
         return;
     }
 }
@@ -335,14 +336,8 @@ __device__ __forceinline__ bool upstream_solid(int wf, bool zlo, bool zhi) {
     return s;
 }
 
-// Blocks of the tiled kernels that one CU holds at once: bounded by LDS
-// (160 KB per CU) and by the waves the register budget allows (4 SIMDs x
-// TSLB_WAVES_PER_EU waves).
-constexpr int kLdsBytes = NSLOT * LY * LX * 4;
-constexpr int kBlocksPerCu = (163840 / kLdsBytes) < ((4 * TSLB_WAVES_PER_EU) / (NTHREADS / 64))
-                                 ? (163840 / kLdsBytes)
-                                 : ((4 * TSLB_WAVES_PER_EU) / (NTHREADS / 64));
-static_assert(kBlocksPerCu >= 1, "a tile must fit one CU");
+// A tile's exchange fits a CU's LDS; one block runs per CU.
+static_assert(NSLOT * LY * LX * 4 <= 163840, "a tile must fit one CU");
 
 // Work list of the tiled update.  Every block of the grid marches a short
 // list of column segments (tile column, first plane, end plane); a segment
@@ -424,15 +419,26 @@ inline Schedule schedule_for(int columns, int nz, int resident, int tz, int spli
     return s;
 }
 
+// The least (cost, segments per block, tz, split).  Most of them are ruled out
+// without dealing their tiles: a cost is at least the mean over the blocks
+// (every segment costs its planes and 2 more) and at least the longest segment,
+// and one of the height that would fill each block once bounds it from above.
 inline Schedule build_schedule(int columns, int nz, int resident) {
     int best_tz = 1, best_split = 1;
     long long best_cost = -1;
     int best_nseg = 0;
-    for (int tz = 1; tz <= 64 && tz <= nz; ++tz) {
-        const long long left = ((long long)columns * ((nz + tz - 1) / tz)) % resident;
-        for (int split = 1; split <= (left ? std::min(tz, 8) : 1); ++split) {
+    const int fill = std::min({64, nz, (int)std::max(1LL, ((long long)columns * nz + resident - 1) / resident)});
+    long long bound = schedule_for(columns, nz, resident, fill, 1, false).cost;
+    for (int tz = std::min(64, nz); tz >= 1; --tz) {
+        const long long tiles = (long long)columns * ((nz + tz - 1) / tz), left = tiles % resident;
+        const long long mean = ((long long)columns * nz + 2 * tiles + resident - 1) / resident;
+        if (mean > bound) continue;
+        for (int split = left ? std::min(tz, 8) : 1; split >= 1; --split) {
+            if ((tiles >= resident ? tz : (tz + split - 1) / split) + 2 > bound) continue;
             const Schedule s = schedule_for(columns, nz, resident, tz, split, false);
-            if (best_cost < 0 || s.cost < best_cost || (s.cost == best_cost && s.nseg < best_nseg)) {
+            bound = std::min(bound, s.cost);
+            // visited from the largest (tz, split) down: of equals the last stays
+            if (best_cost < 0 || s.cost < best_cost || (s.cost == best_cost && s.nseg <= best_nseg)) {
                 best_cost = s.cost;
                 best_nseg = s.nseg;
                 best_tz = tz;

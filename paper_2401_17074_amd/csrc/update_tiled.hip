@@ -15,17 +15,63 @@ bool tiled_writes_x_ghosts_bf16(const StepParams& p);
 int tiled_columns_f32(const Geometry& g);
 int tiled_columns_f16(const Geometry& g);
 int tiled_columns_bf16(const Geometry& g);
+hipError_t launch_update_tiled_rows8_f32(const void* in, void* out, const StepParams& p, hipStream_t s);
+hipError_t launch_update_tiled_rows13_f16(const void* in, void* out, const StepParams& p, hipStream_t s);
+hipError_t launch_update_tiled_rows13_bf16(const void* in, void* out, const StepParams& p, hipStream_t s);
+int tiled_columns_rows8_f32(const Geometry& g);
+int tiled_columns_rows13_f16(const Geometry& g);
+int tiled_columns_rows13_bf16(const Geometry& g);
 
-hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg,
+// Tiles of 12 rows, or of another height:
+// FP32, 8 rows: a block has 11 waves in place of 15, so each of its plane-steps
+// is shorter, and it needs more of them.  Taken where it needs at most one
+// more: on small grids, where the chain of steps is the time, and where 8 rows
+// divide the grid better (us per step, 12 rows / 8; plane-steps in brackets:
+// 64^3 10.1 (4) / 8.7 (4), 64 x 64 x 128 13.6 (6) / 12.2 (6), 80^3 15.3 (7) /
+// 17.8 (9), 96^3 18.2 (8) / 20.4 (11); adjoint step of 64^3 11.5 / 10.5).
+// 16-bit storage, 13 rows: a block has 16 waves in place of 15, so fewer halo
+// columns per node, but no SIMD with a wave less.  Taken where two levels
+// exceed the Infinity Cache (us per step, 12 rows / 13, channel FP16: 512 x 256
+// x 256 393 / 383, 384 x 192 x 192 180 / 175, 333 x 210 x 140 141 / 138; below,
+// 128^3 30.7 / 33.5, 249 x 166 x 108 63.7 / 66.6; FP32, bound by memory, keeps
+// 12: 512 x 256 x 256 538 / 557), or where they exceed L2 and 13 rows save 15 %
+// of the plane-steps (200 x 150 x 100 52.1 / 51.0; jet 160 x 64 x 320 BF16 77.2
+// / 72.2).  Levels that fit L2 keep 12: a node next to a tile's border receives
+// populations that are equal up to rounding only, and a moved rounding of a
+// 16-bit value is a whole storage ulp in the field that a caller reads back.
+hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, int& other_rows,
                           long long& steps) {
-    const int columns = storage == 0 ? tiled_columns_f32(g) : storage == 1 ? tiled_columns_f16(g) : tiled_columns_bf16(g);
     const int resident = (compute_units() + 7) & ~7;  // one block per CU
-    Schedule s = build_schedule(columns, g.n[2], resident);
+    const int columns = storage == 0 ? tiled_columns_f32(g) : storage == 1 ? tiled_columns_f16(g) : tiled_columns_bf16(g);
+    const int other = storage == 0   ? tiled_columns_rows8_f32(g)
+                      : storage == 1 ? tiled_columns_rows13_f16(g)
+                                     : tiled_columns_rows13_bf16(g);
+    Schedule s;
+    if (storage == 0) {
+        s = build_schedule(columns, g.n[2], resident);
+        steps = s.cost;
+        // a list's cost is at least the mean over its blocks
+        other_rows = ((long long)other * g.n[2] + resident - 1) / resident + 2 <= s.cost + 1;
+        if (other_rows) {
+            Schedule s8 = build_schedule(other, g.n[2], resident);
+            other_rows = s8.cost <= s.cost + 1;
+            if (other_rows) s = std::move(s8);
+        }
+    } else {
+        const size_t levels = 2 * 20 * (size_t)g.N;
+        other_rows = levels > kInfinityCacheBytes;
+        s = build_schedule(other_rows ? other : columns, g.n[2], resident);
+        if (!other_rows && levels > kL2Bytes) {
+            Schedule s13 = build_schedule(other, g.n[2], resident);
+            other_rows = 20 * s13.cost <= 17 * s.cost;
+            if (other_rows) s = std::move(s13);
+        }
+        steps = s.cost;
+    }
     if (s.grid < 8 || s.nseg < 1) return hipErrorInvalidValue;
     seg = std::move(s.seg);
     grid = s.grid;
     nseg = s.nseg;
-    steps = s.cost;
     return hipSuccess;
 }
 
@@ -40,9 +86,9 @@ bool tiled_writes_x_ghosts(int storage, const StepParams& p) {
 
 hipError_t launch_update_tiled(int storage, const void* in, void* out, const StepParams& p, hipStream_t s) {
     switch (storage) {
-    case 0: return launch_update_tiled_f32(in, out, p, s);
-    case 1: return launch_update_tiled_f16(in, out, p, s);
-    case 2: return launch_update_tiled_bf16(in, out, p, s);
+    case 0: return p.sched_other_rows ? launch_update_tiled_rows8_f32(in, out, p, s) : launch_update_tiled_f32(in, out, p, s);
+    case 1: return p.sched_other_rows ? launch_update_tiled_rows13_f16(in, out, p, s) : launch_update_tiled_f16(in, out, p, s);
+    case 2: return p.sched_other_rows ? launch_update_tiled_rows13_bf16(in, out, p, s) : launch_update_tiled_bf16(in, out, p, s);
     }
     return hipErrorInvalidValue;
 }

@@ -183,6 +183,12 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
             gl[a] = WALLS ? on * f : f;
         }
         coefficients<ORDER, LAT>(m, gl, kSize == 4 ? omo : omo * p.inv_scale[2], A);
+        // no multiplication of the coefficients is fused into the evaluation
+        // that follows, which differs between the roles
+        if constexpr (ORDER == 2 && LAT == 27) {
+#pragma unroll
+            for (int k = K000; k <= K011; ++k) asm volatile("" : "+v"(A[k]));
+        }
     };
     if (wave >= NINT / 64) {
         // ------------------------------------------------------- halo waves
@@ -381,6 +387,9 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
                     build(arrived<S>(rcur, m), gv, c.gon, zp, omo, A);
                 populations<LAT, !kDeferWeights>(A, G);
             }
+            // the value that stays is rounded with its weight 12, like those
+            // that go through LDS
+            if constexpr (LAT == 19) asm volatile("" : "+v"(G[13]));
             if constexpr (WALLS && PART == 0) {
                 // half-way bounce-back in place: a fluid node next to a wall
                 // receives its own population along -c for every c whose

@@ -81,7 +81,7 @@ def test_bricks(kind, nx, xface):
     _check(kind, nx, 13, 5, xface)
 
 
-# tiles of 64 x 12 (FP32) or 64 x 13, 37 rows one past a tile of 12, segments of one and two planes
+# tiles of 64 x 12 (FP32: x 8), 37 rows one past a tile, segments of a few planes
 @pytest.mark.parametrize("kind", [0, 1, 2])
 @pytest.mark.parametrize("nx", [63, 64, 65, 130])
 @pytest.mark.parametrize("xface", [P, X, O])
@@ -130,6 +130,14 @@ def test_other_lattice_and_order(lattice, order, dims):
     assert np.all(np.abs(got - want)[:, fl] <= 16 * EPS32 * np.array(size)[:, None])
 
 
+# tiles of 64 x 12: 37 rows one past a tile
+@pytest.mark.parametrize("kind", [0, 1, 2])
+@pytest.mark.parametrize("nx", [64, 65])
+@pytest.mark.parametrize("xface", [P, X, O])
+def test_larger_tiles(kind, nx, xface):
+    _check(kind, nx, 37, 607, xface)
+
+
 # FP32 levels larger than the Infinity Cache (268 MB): non-temporal stores and
 # loads two planes ahead, segments of odd and even length
 @pytest.mark.parametrize("xface", [P, X, O])
@@ -137,15 +145,16 @@ def test_streamed_tiles(xface):
     _check(0, 64, 130, 413, xface)
 
 
-# tiles of 64 x 13 (16-bit storage): 40 rows one past a tile
+# tiles of 64 x 13 (16-bit levels larger than the Infinity Cache, 270 MB): 40
+# rows one past a tile
 @pytest.mark.parametrize("kind", [1, 2])
-@pytest.mark.parametrize("xface", [P, X, O])
+@pytest.mark.parametrize("xface", [P, X])
 def test_thirteen_row_tiles(kind, xface):
-    _check(kind, 65, 40, 101, xface)
+    _check(kind, 65, 40, 2600, xface)
 
 
 @pytest.mark.parametrize("field", [False, True])
-@pytest.mark.parametrize("dims", [(1, 13, 5), (63, 12, 9), (64, 25, 4), (130, 37, 101), (66, 70, 203)])
+@pytest.mark.parametrize("dims", [(1, 13, 5), (63, 12, 9), (64, 25, 4), (130, 37, 101), (66, 70, 203), (65, 37, 607)])
 @pytest.mark.parametrize("xface", [P, X, O])
 def test_adjoint(dims, field, xface):
     """One adjoint step where tiles, segments and roles meet an edge, with and
