@@ -423,12 +423,14 @@ inline Schedule schedule_for(int columns, int nz, int resident, int tz, int spli
 // without dealing their tiles: a cost is at least the mean over the blocks
 // (every segment costs its planes and 2 more) and at least the longest segment,
 // and one of the height that would fill each block once bounds it from above.
-inline Schedule build_schedule(int columns, int nz, int resident) {
+// With a limit >= 0: an empty schedule if none costs that or less.
+inline Schedule build_schedule(int columns, int nz, int resident, long long limit = -1) {
     int best_tz = 1, best_split = 1;
     long long best_cost = -1;
     int best_nseg = 0;
     const int fill = std::min({64, nz, (int)std::max(1LL, ((long long)columns * nz + resident - 1) / resident)});
     long long bound = schedule_for(columns, nz, resident, fill, 1, false).cost;
+    if (limit >= 0) bound = std::min(bound, limit);
     for (int tz = std::min(64, nz); tz >= 1; --tz) {
         const long long tiles = (long long)columns * ((nz + tz - 1) / tz), left = tiles % resident;
         const long long mean = ((long long)columns * nz + 2 * tiles + resident - 1) / resident;
@@ -436,7 +438,8 @@ inline Schedule build_schedule(int columns, int nz, int resident) {
         for (int split = left ? std::min(tz, 8) : 1; split >= 1; --split) {
             if ((tiles >= resident ? tz : (tz + split - 1) / split) + 2 > bound) continue;
             const Schedule s = schedule_for(columns, nz, resident, tz, split, false);
-            bound = std::min(bound, s.cost);
+            if (s.cost > bound) continue;
+            bound = s.cost;
             // visited from the largest (tz, split) down: of equals the last stays
             if (best_cost < 0 || s.cost < best_cost || (s.cost == best_cost && s.nseg <= best_nseg)) {
                 best_cost = s.cost;
@@ -446,6 +449,7 @@ inline Schedule build_schedule(int columns, int nz, int resident) {
             }
         }
     }
+    if (best_cost < 0) return Schedule{};  // above the limit
     return schedule_for(columns, nz, resident, best_tz, best_split, true);
 }
 

@@ -50,20 +50,16 @@ hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg
     if (storage == 0) {
         s = build_schedule(columns, g.n[2], resident);
         steps = s.cost;
-        // a list's cost is at least the mean over its blocks
-        other_rows = ((long long)other * g.n[2] + resident - 1) / resident + 2 <= s.cost + 1;
-        if (other_rows) {
-            Schedule s8 = build_schedule(other, g.n[2], resident);
-            other_rows = s8.cost <= s.cost + 1;
-            if (other_rows) s = std::move(s8);
-        }
+        Schedule s8 = build_schedule(other, g.n[2], resident, s.cost + 1);
+        other_rows = s8.grid > 0;
+        if (other_rows) s = std::move(s8);
     } else {
         const size_t levels = 2 * 20 * (size_t)g.N;
         other_rows = levels > kInfinityCacheBytes;
         s = build_schedule(other_rows ? other : columns, g.n[2], resident);
         if (!other_rows && levels > kL2Bytes) {
-            Schedule s13 = build_schedule(other, g.n[2], resident);
-            other_rows = 20 * s13.cost <= 17 * s.cost;
+            Schedule s13 = build_schedule(other, g.n[2], resident, 17 * s.cost / 20);
+            other_rows = s13.grid > 0;
             if (other_rows) s = std::move(s13);
         }
         steps = s.cost;
