@@ -199,6 +199,31 @@ __device__ __forceinline__ void populations(const float A[NK], float G[27]) {
                                   A[K020] - A[K021], A[K110] - A[K111], A[K210], A[K120], G);
 }
 
+// Frame of the evaluation.  With one velocity component fixed at s = +-1 the
+// polynomial collapses to one in the two others, which is cheaper where only
+// those nine values are of use, and rounds differently.  So that a node's
+// update does not depend on the kernel, tile height or brick that does it, a
+// D3Q27 population is evaluated collapsed where it crosses a border of the
+// grid's cells of 64 columns x 12 rows (on x if it crosses one there, else on
+// y), and in full everywhere else, on coordinates that are not wrapped yet.
+constexpr int kFrameX = 64, kFrameY = 12;
+// Does what coordinate v sends along +1 (-1) cross a border?
+__host__ __device__ constexpr bool crosses_up(int v, int cell) { return (v + 1) % cell == 0; }
+__host__ __device__ constexpr bool crosses_down(int v, int cell) { return v % cell == 0; }
+
+// D3Q27 populations (without weights) with cy = s: Q[9 + 3 (cz + 1) + (cx + 1)].
+__device__ __forceinline__ void collapsed_y(const float A[NK], float s, float Q[27]) {
+    eval_slice<0, 27, false>(fmaf(s, A[K010], A[K000] + A[K020]), fmaf(s, A[K110], A[K100] + A[K120]),
+                             fmaf(s, A[K011], A[K001] + A[K021]), fmaf(s, A[K210], A[K200]), fmaf(s, A[K012], A[K002]),
+                             fmaf(s, A[K111], A[K101]), A[K201], A[K102], Q);
+}
+// With cx = s: Q[9 + 3 (cz + 1) + (cy + 1)].
+__device__ __forceinline__ void collapsed_x(const float A[NK], float s, float Q[27]) {
+    eval_slice<0, 27, false>(fmaf(s, A[K100], A[K000] + A[K200]), fmaf(s, A[K110], A[K010] + A[K210]),
+                             fmaf(s, A[K101], A[K001] + A[K201]), fmaf(s, A[K120], A[K020]), fmaf(s, A[K102], A[K002]),
+                             fmaf(s, A[K111], A[K011]), A[K021], A[K012], Q);
+}
+
 // Moments of one arriving cz slice F[cy+1][cx+1], added to the output plane
 // accumulator: sum F, sum F c and sum F c c with c = (cx, cy, CZ).  With
 // WEIGHTS the values arrive without their lattice weight and the D3Q27

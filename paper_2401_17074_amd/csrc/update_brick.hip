@@ -56,8 +56,13 @@ __global__ void __launch_bounds__(kBrickThreads, 6)
 
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // coordinates in the brick with its halo
-    enum { kNode, kZ, kY, kX };
+    // Coordinates in the brick with its halo, and what of the node's
+    // populations is published: all (its own nodes), or the nine with one
+    // component fixed, evaluated in full or collapsed as the frame of the
+    // evaluation has it (see crosses_up; its borders are borders of bricks).
+    enum { kNode, kFullX, kFullY, kFullZ, kX, kY };
+    static_assert(kFrameX % BX == 0 && kFrameY % BY == 0, "bricks lie within cells of the frame");
+    const bool ylo_frame = crosses_up(y0 - 1, kFrameY), yhi_frame = crosses_down(y0 + BY, kFrameY);
     int hx, hy, hz, role = kNode;
     bool on = true;
     if (wave < 4) {
@@ -65,27 +70,29 @@ __global__ void __launch_bounds__(kBrickThreads, 6)
         hy = 1 + lane / BX;
         hz = 1 + wave;
     } else if (wave < 6) {
-        role = kZ;
+        role = kFullZ;
         hx = 1 + (lane & (BX - 1));
         hy = 1 + lane / BX;
         hz = wave == 4 ? 0 : HZ - 1;
     } else if (wave < 8) {
-        role = kY;
         hx = 1 + (lane & (BX - 1));
         hy = wave == 6 ? 0 : HY - 1;
         hz = 1 + lane / BX;
-    } else if (wave == 8) {
-        role = kZ;  // an edge along x
+        role = (wave == 6 ? ylo_frame : yhi_frame) ? kY : kFullY;
+    } else if (wave == 8) {  // the edges along x
         hx = 1 + (lane & (BX - 1));
         hy = (lane & BX) ? HY - 1 : 0;
         hz = (lane & (2 * BX)) ? HZ - 1 : 0;
+        role = (hy == 0 ? ylo_frame : yhi_frame) ? kY : kFullZ;
     } else {
-        role = kX;
         const int k = (wave - 9) * 64 + lane;  // 36 nodes at each end
         on = k < 2 * HY * HZ;
         hx = k < HY * HZ ? 0 : HX - 1;
         hy = k % HY;
         hz = k / HY % HZ;
+        const bool xf = hx == 0 ? crosses_up(x0 - 1, kFrameX) : crosses_down(x0 + BX, kFrameX);
+        const bool yf = (hy == 0 && ylo_frame) || (hy == HY - 1 && yhi_frame);
+        role = xf ? kX : yf ? kY : kFullX;
     }
     float G[27];
     const int x = x0 - 1 + hx, y = y0 - 1 + hy, z = z0 - 1 + hz;
@@ -119,46 +126,57 @@ __global__ void __launch_bounds__(kBrickThreads, 6)
         const float omo = omo_at(p, wz);
         float A[NK];
         coefficients<ORDER, LAT>(m, gl, kSize == 4 ? omo : omo * p.inv_scale[2], A);
-        // what a halo node sends into the brick has one velocity component
-        // fixed at s = +-1: the polynomial in the two others, on their 3 x 3
-        // grid Q[18 + 3 (later) + (earlier)]
         float* const w = &lds[0][own];
-        auto put = [&]<int I>(float* base, float v, bool carried) {
-            if (carried) base[I * kBrickNodes] = v;
-        };
-        if (role == kNode) {
-            populations<LAT, !kDeferWeights>(A, G);
+        if constexpr (LAT == 19) {
+            // evaluated in full by every node, as in the tiled update
+            populations<19, true>(A, G);
+            // the value that stays is rounded with its weight 12 (see there)
+            asm volatile("" : "+v"(G[13]));
             Unroll<0, 27>::run([&]<int I>() {
-                if constexpr (carries<LAT>(I) && I != 13) w[I * kBrickNodes] = G[I];
-            });
-        } else if (role == kZ) {
-            const float s = hz == 0 ? 1.0f : -1.0f;
-            eval_slice<1, LAT, !kDeferWeights>(fmaf(s, A[K001], A[K000] + A[K002]), fmaf(s, A[K101], A[K100] + A[K102]),
-                                               fmaf(s, A[K011], A[K010] + A[K012]), fmaf(s, A[K201], A[K200]),
-                                               fmaf(s, A[K021], A[K020]), fmaf(s, A[K111], A[K110]), A[K210], A[K120],
-                                               G);
-            float* const b9 = w + (hz == 0 ? 18 : 0) * kBrickNodes;
-            Unroll<0, 9>::run([&]<int I>() { put.template operator()<I>(b9, G[18 + I], carries<LAT>(18 + I)); });
-        } else if (role == kY) {
-            const float s = hy == 0 ? 1.0f : -1.0f;
-            eval_slice<1, LAT, !kDeferWeights>(fmaf(s, A[K010], A[K000] + A[K020]), fmaf(s, A[K110], A[K100] + A[K120]),
-                                               fmaf(s, A[K011], A[K001] + A[K021]), fmaf(s, A[K210], A[K200]),
-                                               fmaf(s, A[K012], A[K002]), fmaf(s, A[K111], A[K101]), A[K201], A[K102],
-                                               G);
-            float* const b9 = w + (hy == 0 ? 6 : 0) * kBrickNodes;
-            Unroll<0, 9>::run([&]<int I>() {
-                put.template operator()<9 * (I / 3) + I % 3>(b9, G[18 + I], carries<LAT>(9 * (I / 3) + I % 3));
+                if constexpr (carries<19>(I) && I != 13) w[I * kBrickNodes] = G[I];
             });
         } else {
-            const float s = hx == 0 ? 1.0f : -1.0f;
-            eval_slice<1, LAT, !kDeferWeights>(fmaf(s, A[K100], A[K000] + A[K200]), fmaf(s, A[K110], A[K010] + A[K210]),
-                                               fmaf(s, A[K101], A[K001] + A[K201]), fmaf(s, A[K120], A[K020]),
-                                               fmaf(s, A[K102], A[K002]), fmaf(s, A[K111], A[K011]), A[K021], A[K012],
-                                               G);
-            float* const b9 = w + (hx == 0 ? 2 : 0) * kBrickNodes;
-            Unroll<0, 9>::run([&]<int I>() {
-                put.template operator()<9 * (I / 3) + 3 * (I % 3)>(b9, G[18 + I], carries<LAT>(9 * (I / 3) + 3 * (I % 3)));
-            });
+            // no multiplication of the coefficients is fused into the
+            // evaluation that follows, which differs between the roles
+            if constexpr (ORDER == 2) {
+#pragma unroll
+                for (int k = K000; k <= K011; ++k) asm volatile("" : "+v"(A[k]));
+            }
+            // the nine populations with component D (0 x, 1 y, 2 z) positive
+            // where `low`, negative otherwise; value(I) of the velocity I
+            auto put = [&]<int D>(bool low, auto&& value) {
+                constexpr int kStep[3] = {1, 3, 9};
+                float* const base = w + (low ? 2 * kStep[D] : 0) * kBrickNodes;
+                Unroll<0, 27>::run([&]<int I>() {
+                    constexpr int c[3] = {cx_of(I), cy_of(I), cz_of(I)};
+                    if constexpr (c[D] == -1) base[I * kBrickNodes] = value.template operator()<I, I + 2 * kStep[D]>();
+                });
+            };
+            float Q[27];
+            if (role == kNode || role == kFullX || role == kFullY) {
+                populations<27, false>(A, G);
+                if (role == kNode)
+                    Unroll<0, 27>::run([&]<int I>() {
+                        if constexpr (I != 13) w[I * kBrickNodes] = G[I];
+                    });
+                else if (role == kFullX)
+                    put.template operator()<0>(hx == 0, [&]<int M, int P>() { return hx == 0 ? G[P] : G[M]; });
+                else
+                    put.template operator()<1>(hy == 0, [&]<int M, int P>() { return hy == 0 ? G[P] : G[M]; });
+            } else if (role == kFullZ) {
+                // the slice cz = s of populations()
+                const float s = hz == 0 ? 1.0f : -1.0f;
+                eval_slice<1, 27, false>(fmaf(s, A[K001], A[K000] + A[K002]), fmaf(s, A[K101], A[K100] + A[K102]),
+                                         fmaf(s, A[K011], A[K010] + A[K012]), fmaf(s, A[K201], A[K200]),
+                                         fmaf(s, A[K021], A[K020]), fmaf(s, A[K111], A[K110]), A[K210], A[K120], Q);
+                put.template operator()<2>(hz == 0, [&]<int M, int P>() { return Q[P]; });
+            } else if (role == kY) {
+                collapsed_y(A, hy == 0 ? 1.0f : -1.0f, Q);
+                put.template operator()<1>(hy == 0, [&]<int M, int P>() { return Q[9 + 3 * (cz_of(M) + 1) + cx_of(M) + 1]; });
+            } else {
+                collapsed_x(A, hx == 0 ? 1.0f : -1.0f, Q);
+                put.template operator()<0>(hx == 0, [&]<int M, int P>() { return Q[9 + 3 * (cz_of(M) + 1) + cy_of(M) + 1]; });
+            }
         }
     }
     __syncthreads();
@@ -176,15 +194,17 @@ __global__ void __launch_bounds__(kBrickThreads, 6)
         else
             F[Z + 1][Y + 1][X + 1] = lds[I][own - X - HX * (Y + HY * Z)];
     });
-    if (WALLS && (wf != 0 || zlo || zhi)) {
-        // half-way bounce-back: the node's own population along -c comes back
-        // where the upstream node is a wall (of equal weight)
-        Unroll<0, 27>::run([&]<int I>() {
-            if (upstream_solid<I>(wf, zlo, zhi)) F[cz_of(I) + 1][cy_of(I) + 1][cx_of(I) + 1] = G[26 - I];
-        });
-    }
     MomentSums a;
     add_slice<1, true, kDeferWeights>(F[2], a);
+    if (WALLS && (wf != 0 || zlo || zhi)) {
+        // half-way bounce-back: the node's own population along -c comes back
+        // where the upstream node is a wall (of equal weight), whose own are
+        // zero; added where the tiled update adds them
+        Unroll<0, 27>::run([&]<int I>() {
+            if constexpr (carries<LAT>(I))
+                if (upstream_solid<I>(wf, zlo, zhi)) a.template add<I>(kDeferWeights ? w216_of(I) * G[26 - I] : G[26 - I]);
+        });
+    }
     add_slice<0, false, kDeferWeights>(F[1], a);
     add_slice<-1, false, kDeferWeights>(F[0], a);
     float o[10];
@@ -231,10 +251,8 @@ hipError_t launch_s(const void* in, void* out, const StepParams& p, hipStream_t 
 // 8.3 / 4.6, 48^3 (2, 3) 8.7 / 6.0, 50^3 (3, 3) 8.2 / 8.8, 56^3 (4, 4) 10.0 /
 // 9.4, 16 x 90 x 90 (3, 5) 11.3 / 7.4, 64^3 (4, 4) 10.5 / 11.0, 96^3 (14, 8)
 // 21.2 / 27.9.
-// FP32 only: bricks and tiles round a halo's populations differently, and a
-// moved rounding of a 16-bit value is a whole storage ulp in the field that a
-// caller reads back (1e-4 of it where FP32 fields agree to 1e-7), so 16-bit
-// fields are left to the kernel that has always updated them.
+// The values do not depend on the choice (see crosses_up).  FP32 only: 16-bit
+// grids were not moved to bricks.
 bool prefers_brick(int storage, const Geometry& g, long long steps) {
     const long long bricks = (long long)((g.n[0] + BX - 1) / BX) * ((g.n[1] + BY - 1) / BY) * ((g.n[2] + BZ - 1) / BZ);
     const long long rounds = (bricks + compute_units() - 1) / compute_units();

@@ -36,9 +36,8 @@ int tiled_columns_rows13_bf16(const Geometry& g);
 // 128^3 30.7 / 33.5, 249 x 166 x 108 63.7 / 66.6; FP32, bound by memory, keeps
 // 12: 512 x 256 x 256 538 / 557), or where they exceed L2 and 13 rows save 15 %
 // of the plane-steps (200 x 150 x 100 52.1 / 51.0; jet 160 x 64 x 320 BF16 77.2
-// / 72.2).  Levels that fit L2 keep 12: a node next to a tile's border receives
-// populations that are equal up to rounding only, and a moved rounding of a
-// 16-bit value is a whole storage ulp in the field that a caller reads back.
+// / 72.2).  Levels that fit L2 keep 12.  The values do not depend on
+// the height (see crosses_up).
 hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, int& other_rows,
                           long long& steps) {
     const int resident = (compute_units() + 7) & ~7;  // one block per CU

@@ -134,6 +134,14 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
     // 181 x 428 x 145 220 against 212 us).  16-bit: one set, converted out of
     // as it arrives and reloaded at once, a whole plane-step ahead.
     constexpr bool kTwo = kSize == 4 && NT, kOne = kSize == 4 && !NT;
+    // Tiles whose rows are not the frame's (see crosses_up): the rows on both
+    // sides of a border of the frame evaluate one slice twice, the halo rows
+    // elsewhere theirs in full.  Halo rows collapsed at every tile border were
+    // faster with walls (FP16 channels 512 x 256 x 256 378 us, now 389, 384 x
+    // 192 x 192 173 and 179) and as fast without (256^3 FP16 189, 187; 64^3
+    // FP32 8.9, 9.0), but their values depended on the tile height.
+    constexpr bool kOtherRows = kDeferWeights && TY != kFrameY;
+    static_assert(TX == kFrameX);
     const Geometry& g = p.geo;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
     const bool pz = (g.periodic & 4) != 0;
@@ -213,11 +221,14 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
         struct Column {
             unsigned node;  // node in plane, wrapped or clamped
             float gon;
+            int row;  // the first one above the border of the tile, in the frame's cell (see crosses_up)
         };
         auto column = [&](int col_id) {
+            const int y0 = (col_id / tiles_x) * TY;
             const int wx = wrap_or_clamp((col_id % tiles_x) * TX - 1 + lx, nx, g.periodic & 1);
-            const int wy = wrap_or_clamp((col_id / tiles_x) * TY - 1 + ly, ny, g.periodic & 2);
-            return Column{(unsigned)wx + (unsigned)nx * (unsigned)wy, solid_col(wx, wy) ? 0.0f : 1.0f};
+            const int wy = wrap_or_clamp(y0 - 1 + ly, ny, g.periodic & 2);
+            return Column{(unsigned)wx + (unsigned)nx * (unsigned)wy, solid_col(wx, wy) ? 0.0f : 1.0f,
+                          (kind == 1 ? y0 : y0 + TY) % kFrameY};
         };
         Raw r[10];
         float m[10];
@@ -247,34 +258,38 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
             for (int zp = zs - 1; zp <= ze; ++zp) {
                 float A[NK];
                 build(arrived<S>(r, m), gv, c.gon, zp, omo, A);
-                // The nine populations a halo column sends into the tile.  On
-                // D3Q27, with one velocity component fixed at s = +-1 (cy for
-                // the rows, cx for the corners and sides), the polynomial
-                // collapses to one in the two other components, evaluated on
-                // their 3 x 3 grid.
+                // The nine populations a halo column sends into the tile: the
+                // side columns' and corners' collapsed on x, the rows'
+                // collapsed on y at a border of the frame, else in full.
                 auto put = [&]<int I>(float v) { w[slot_of(I) * LY * LX] = v; };
                 if constexpr (kDeferWeights) {
-                    float Q[27];  // Q[9 + 3 (cz + 1) + (other + 1)]
+                    float Q[27];
                     if (kind != 3) {
-                        const float s = kind == 1 ? 1.0f : -1.0f;  // cy
-                        eval_slice<0, 27, false>(fmaf(s, A[K010], A[K000] + A[K020]), fmaf(s, A[K110], A[K100] + A[K120]),
-                                                 fmaf(s, A[K011], A[K001] + A[K021]), fmaf(s, A[K210], A[K200]),
-                                                 fmaf(s, A[K012], A[K002]), fmaf(s, A[K111], A[K101]), A[K201], A[K102],
-                                                 Q);
-                        if (kind == 1)
-                            Unroll<0, 27>::run([&]<int I>() {
-                                if constexpr (cy_of(I) == 1) put.template operator()<I>(Q[9 + 3 * (cz_of(I) + 1) + cx_of(I) + 1]);
-                            });
+                        auto rows = [&]<bool COLLAPSED>() {
+                            if constexpr (COLLAPSED)
+                                collapsed_y(A, kind == 1 ? 1.0f : -1.0f, Q);
+                            else
+                                populations<27, false>(A, Q);
+                            auto value = [&](int I) {
+                                return Q[COLLAPSED ? 9 + 3 * (cz_of(I) + 1) + cx_of(I) + 1 : I];
+                            };
+                            if (kind == 1)
+                                Unroll<0, 27>::run([&]<int I>() {
+                                    if constexpr (cy_of(I) == 1) put.template operator()<I>(value(I));
+                                });
+                            else
+                                Unroll<0, 27>::run([&]<int I>() {
+                                    if constexpr (cy_of(I) == -1) put.template operator()<I>(value(I));
+                                });
+                        };
+                        int row = c.row;
+                        if constexpr (kOtherRows) asm volatile("" : "+s"(row));
+                        if (!kOtherRows || row == 0)
+                            rows.template operator()<true>();
                         else
-                            Unroll<0, 27>::run([&]<int I>() {
-                                if constexpr (cy_of(I) == -1) put.template operator()<I>(Q[9 + 3 * (cz_of(I) + 1) + cx_of(I) + 1]);
-                            });
+                            rows.template operator()<false>();
                     } else {
-                        const float s = lx == 0 ? 1.0f : -1.0f;  // cx
-                        eval_slice<0, 27, false>(fmaf(s, A[K100], A[K000] + A[K200]), fmaf(s, A[K110], A[K010] + A[K210]),
-                                                 fmaf(s, A[K101], A[K001] + A[K201]), fmaf(s, A[K120], A[K020]),
-                                                 fmaf(s, A[K102], A[K002]), fmaf(s, A[K111], A[K011]), A[K021], A[K012],
-                                                 Q);
+                        collapsed_x(A, lx == 0 ? 1.0f : -1.0f, Q);
                         if (publish && lx == 0)
                             Unroll<0, 27>::run([&]<int I>() {
                                 if constexpr (cx_of(I) == 1) put.template operator()<I>(Q[9 + 3 * (cz_of(I) + 1) + cy_of(I) + 1]);
@@ -359,6 +374,8 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
                                !(gy == ny - 1 && ((g.hi_solid | g.hi_ghost) & 2));
         const bool col_fluid = row_fluid && gx < nx && !(gx == 0 && ((g.lo_solid | g.lo_ghost) & 1)) &&
                                !(gx == nx - 1 && ((g.hi_solid | g.hi_ghost) & 1));
+        // do this row's populations with cy = +1 (-1) cross a border of the frame?
+        const int frame_row = gy % kFrameY;
         const bool xwalls = WALLS && ((g.lo_solid | g.hi_solid) & 1) != 0;
         const bool ylo = WALLS && (g.lo_solid & 2) && gy == 1, yhi = WALLS && (g.hi_solid & 2) && gy == ny - 2;
         const bool xlo = WALLS && (g.lo_solid & 1) && gx == 1, xhi = WALLS && (g.hi_solid & 1) && gx == nx - 2;
@@ -378,6 +395,10 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
             const int z1 = plane_index(on ? zp + 1 : (more ? tn.y - 1 : ze), nz, pz);
             if constexpr (!kTwo && !kOne) load_raw<S>(in_plane(z1), stride, (on ? c.node : cn.node) * kSize, rcur);
             const float omo1 = omo_of(z1);
+            // (compared here: kept as masks across the planes they spill)
+            int row = frame_row;
+            if constexpr (kOtherRows) asm volatile("" : "+s"(row));
+            const bool up = kOtherRows && row == kFrameY - 1, down = kOtherRows && row == 0;
             float G[27];
             {
                 float A[NK];
@@ -386,6 +407,19 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
                 else
                     build(arrived<S>(rcur, m), gv, c.gon, zp, omo, A);
                 populations<LAT, !kDeferWeights>(A, G);
+                if constexpr (kOtherRows) {
+                    // the buffer is free since the previous plane's second barrier
+                    auto collapsed_row = [&]<int CY>() {
+                        float Q[27];
+                        collapsed_y(A, CY, Q);
+                        Unroll<0, 27>::run([&]<int I>() {
+                            if constexpr (cy_of(I) == CY && moves(I))
+                                lds[slot_of(I)][ly][lx] = Q[9 + 3 * (cz_of(I) + 1) + cx_of(I) + 1];
+                        });
+                    };
+                    if (up) collapsed_row.template operator()<1>();
+                    if (down) collapsed_row.template operator()<-1>();
+                }
             }
             // the value that stays is rounded with its weight 12, like those
             // that go through LDS
@@ -410,9 +444,14 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
                     });
                 }
             }
-            Unroll<0, 27>::run([&]<int I>() {
-                if constexpr ((cx_of(I) != 0 || cy_of(I) != 0) && moves(I)) lds[slot_of(I)][ly][lx] = G[I];
-            });
+            auto publish = [&]<int CY>() {
+                Unroll<0, 27>::run([&]<int I>() {
+                    if constexpr (cy_of(I) == CY && (cx_of(I) != 0 || CY != 0) && moves(I)) lds[slot_of(I)][ly][lx] = G[I];
+                });
+            };
+            if (!down) publish.template operator()<-1>();
+            publish.template operator()<0>();
+            if (!up) publish.template operator()<1>();
             if constexpr (FIELD) load_force(on ? c.node : cn.node, z1, gv);
             if constexpr (kOne) load_raw<S>(in_plane(z1), stride, (on ? c.node : cn.node) * kSize, rcur);
             if constexpr (kTwo) {
