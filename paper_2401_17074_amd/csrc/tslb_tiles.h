@@ -478,6 +478,23 @@ inline Schedule build_schedule(int columns, int nz, int resident, long long limi
     return schedule_for(columns, nz, resident, best_tz, best_split, true);
 }
 
+// Bricks of the brick update (see update_brick.hip), one block each.
+constexpr int kBrickX = 16, kBrickY = 4, kBrickZ = 4;
+constexpr int kBrickThreads = 704;
+// Most bricks of a launch: HIP takes fewer than 2^32 threads along x.
+constexpr long long kMaxBricks = 1LL << 22;
+static_assert((kMaxBricks + 8) * kBrickThreads < (1LL << 32));
+inline long long brick_count(const Geometry& g) {
+    return (long long)((g.n[0] + kBrickX - 1) / kBrickX) * ((g.n[1] + kBrickY - 1) / kBrickY) *
+           ((g.n[2] + kBrickZ - 1) / kBrickZ);
+}
+// Is grid g updated in bricks, if the work list of its tiles takes `steps`
+// plane-steps on `cus` compute units (see update_brick.hip)?
+inline bool brick_grid(int storage, const Geometry& g, long long steps, int cus) {
+    const long long bricks = brick_count(g), rounds = (bricks + cus - 1) / cus;
+    return storage == 0 && bricks <= kMaxBricks && rounds < steps;
+}
+
 inline int compute_units() {
     static int cus = 0;
     if (cus == 0) {

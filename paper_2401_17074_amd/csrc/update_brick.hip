@@ -18,13 +18,13 @@ namespace {
 
 using namespace tile;
 
-constexpr int BX = 16, BY = 4, BZ = 4;
+constexpr int BX = kBrickX, BY = kBrickY, BZ = kBrickZ;
 constexpr int HX = BX + 2, HY = BY + 2, HZ = BZ + 2;
 constexpr int kBrickNodes = HX * HY * HZ;  // with the halo
 constexpr int kBrickOut = BX * BY * BZ;
 // 4 waves of the brick's nodes, 2 of the z faces, 2 of the y faces, 1 of the
 // four edges along x, 2 of the x faces with all their edges and corners
-constexpr int kBrickThreads = kBrickOut + 2 * 64 + 2 * 64 + 64 + 128;
+static_assert(kBrickThreads == kBrickOut + 2 * 64 + 2 * 64 + 64 + 128);
 static_assert(BX * BY == 64 && BX * BZ == 64 && 4 * BX == 64 && 2 * HY * HZ <= 128, "whole wavefronts per role");
 static_assert(27 * kBrickNodes * 4 * 2 <= 163840, "two bricks per CU");
 
@@ -221,9 +221,9 @@ __global__ void __launch_bounds__(kBrickThreads, 6)
 
 template <class S, bool WALLS, int ORDER, int LAT>
 hipError_t launch_k(const void* in, void* out, const StepParams& p, hipStream_t s) {
-    const int bx = (p.geo.n[0] + BX - 1) / BX, by = (p.geo.n[1] + BY - 1) / BY, bz = (p.geo.n[2] + BZ - 1) / BZ;
-    const long long bricks = (long long)bx * by * bz;
-    if (p.geo.N >= (1LL << 30) || bricks > (1 << 24)) return hipErrorInvalidValue;
+    const int bx = (p.geo.n[0] + BX - 1) / BX, by = (p.geo.n[1] + BY - 1) / BY;
+    const long long bricks = brick_count(p.geo);
+    if (p.geo.N >= (1LL << 30) || bricks > kMaxBricks) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)((bricks + 7) & ~7LL);  // whole runs per XCD
     hipLaunchKernelGGL((update_brick_kernel<S, WALLS, ORDER, LAT>), dim3(grid), dim3(kBrickThreads), 0, s,
                        (const char*)in, (char*)out, p, bx, by, (int)bricks);
@@ -254,9 +254,7 @@ hipError_t launch_s(const void* in, void* out, const StepParams& p, hipStream_t 
 // The values do not depend on the choice (see crosses_up).  FP32 only: 16-bit
 // grids were not moved to bricks.
 bool prefers_brick(int storage, const Geometry& g, long long steps) {
-    const long long bricks = (long long)((g.n[0] + BX - 1) / BX) * ((g.n[1] + BY - 1) / BY) * ((g.n[2] + BZ - 1) / BZ);
-    const long long rounds = (bricks + compute_units() - 1) / compute_units();
-    return storage == 0 && rounds < steps;
+    return brick_grid(storage, g, steps, compute_units());
 }
 
 hipError_t launch_update_brick(const void* in, void* out, const StepParams& p, hipStream_t s) {
