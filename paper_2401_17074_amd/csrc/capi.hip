@@ -213,7 +213,7 @@ int tslb_create(int nx, int ny, int nz, int lattice, float tau, const float forc
         h->p.sched_grid = grid;
         h->p.sched_nseg = nseg;
         h->p.sched_other_rows = other_rows;
-        h->brick = prefers_brick(h->storage, g, steps);
+        h->brick = prefers_brick(h->storage, g, steps, other_rows != 0);
     }
     // rest state: drho = 0, u = 0, Pi = 0 in every format is all-zero bits
     if (hipMemset(h->buf[0], 0, bytes) != hipSuccess || hipMemset(h->buf[1], 0, bytes) != hipSuccess ||

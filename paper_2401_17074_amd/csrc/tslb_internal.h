@@ -26,9 +26,9 @@ hipError_t launch_update_poplayout(int storage, const void* in, void* out, float
 // 12, and the plane-steps of its longest block (FP32: with 12 rows).
 hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, int& other_rows,
                           long long& steps);
-// Update of small FP32 grids; does it beat the tiled update on grid g, whose work
-// list takes `steps` plane-steps?
-bool prefers_brick(int storage, const Geometry& g, long long steps);
+// Update of small or narrow FP32 grids; does it beat the tiled update on grid
+// g, whose work list takes `steps` plane-steps and tiles of 8 or 12 rows?
+bool prefers_brick(int storage, const Geometry& g, long long steps, bool rows8);
 hipError_t launch_update_brick(const void* in, void* out, const StepParams& p, hipStream_t s);
 hipError_t launch_update_tiled(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);
 hipError_t launch_update_d2q9(int storage, const void* in, void* out, const StepParams& p, hipStream_t s);

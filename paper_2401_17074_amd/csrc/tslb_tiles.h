@@ -489,10 +489,13 @@ inline long long brick_count(const Geometry& g) {
            ((g.n[2] + kBrickZ - 1) / kBrickZ);
 }
 // Is grid g updated in bricks, if the work list of its tiles takes `steps`
-// plane-steps on `cus` compute units (see update_brick.hip)?
-inline bool brick_grid(int storage, const Geometry& g, long long steps, int cus) {
+// plane-steps (with 12 rows) on `cus` compute units and its tiles have 8 rows
+// (rows8) or 12 (see update_brick.hip)?
+inline bool brick_grid(int storage, const Geometry& g, long long steps, bool rows8, int cus) {
     const long long bricks = brick_count(g), rounds = (bricks + cus - 1) / cus;
-    return storage == 0 && bricks <= kMaxBricks && rounds < steps;
+    if (storage != 0 || bricks > kMaxBricks) return false;
+    if (rows8) return 3 * rounds <= 2 * steps;
+    return 2 * 40 * (size_t)g.N <= kInfinityCacheBytes ? rounds < steps : 4 * rounds < 3 * steps;
 }
 
 inline int compute_units() {

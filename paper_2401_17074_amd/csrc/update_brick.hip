@@ -244,17 +244,24 @@ hipError_t launch_s(const void* in, void* out, const StepParams& p, hipStream_t 
 
 }  // namespace
 
-// Bricks run in rounds of one per CU (two at a time), a round about 1.6 us
-// after the first 4.6; the marching kernel takes about 5 us and 1.1 us for
-// each plane-step of its longest block (steps: the work list's cost).  us per
-// step of an FP32 periodic grid, marching / bricks: 32^3 (1 round, 3 steps)
-// 8.3 / 4.6, 48^3 (2, 3) 8.7 / 6.0, 50^3 (3, 3) 8.2 / 8.8, 56^3 (4, 4) 10.0 /
-// 9.4, 16 x 90 x 90 (3, 5) 11.3 / 7.4, 64^3 (4, 4) 10.5 / 11.0, 96^3 (14, 8)
-// 21.2 / 27.9.
+// Bricks run in rounds of one per CU (two at a time): about 5 us for one and
+// 1.8 us for each further one (2.3 where two levels exceed the Infinity Cache,
+// for the halo's traffic).  The tiled update takes about 5 us and, with tiles
+// of 8 rows, 1.4 us for each plane-step of its longest block, with 12 rows 1.7
+// (its list's cost in steps).  us per step of FP32 grids, tiles / bricks
+// (rounds, steps):
+//   8 rows: 32^3 6.7 / 5.1 (1, 3), 48^3 8.2 / 6.5 (2, 3), 96 x 32 x 32 7.4 / 6.6
+//   (2, 3), 64 x 4 x 1024 10.9 / 10.9 (4, 6), 48 x 4 x 8192 44.7 / 47.1 (24, 34),
+//   52^3 8.6 / 9.3 (3, 4), 64 x 4 x 12000 63 / 90 (47, 49; 86 in tiles of 12
+//   rows), 16 x 4 x 262144 1342 / 589 (256, 1056);
+//   12 rows: 16 x 200 x 256 36.2 / 27.1 (13, 20), 8 x 500 x 500 146 / 115 (62,
+//   88), 17 x 100 x 100 13.9 / 11.8 (5, 6);
+//   12 rows, beyond the cache: 16 x 64 x 16384 670 / 626 (256, 396), 2 x 4096 x
+//   2048 4517 / 4003 (2048, 2826), 16 x 2000 x 2000 2301 / 2334 (977, 1355).
 // The values do not depend on the choice (see crosses_up).  FP32 only: 16-bit
 // grids were not moved to bricks.
-bool prefers_brick(int storage, const Geometry& g, long long steps) {
-    return brick_grid(storage, g, steps, compute_units());
+bool prefers_brick(int storage, const Geometry& g, long long steps, bool rows8) {
+    return brick_grid(storage, g, steps, rows8, compute_units());
 }
 
 hipError_t launch_update_brick(const void* in, void* out, const StepParams& p, hipStream_t s) {

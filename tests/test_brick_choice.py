@@ -45,3 +45,12 @@ def test_small_grids_in_bricks(choose):
         assert r[4], r
     for r in choose([(64, 64, 64), (96, 96, 96), (256, 256, 256), (384, 192, 192)]):
         assert not r[4], r
+
+
+def test_narrow_grids_by_time(choose):
+    """Bricks only where they were measured to be no slower than the tiles."""
+    for r in choose([(16, 4, 262144), (3, 3, 1 << 20), (8, 500, 500), (17, 100, 100), (16, 200, 256), (64, 4, 1024)]):
+        assert r[4], r
+    for r in choose([(64, 4, 4096), (64, 4, 12000), (64, 1, 16384), (48, 4, 12000), (128, 4, 4096), (512, 4, 1024),
+                     (52, 52, 52), (64, 4, 65536)]):
+        assert not r[4], r
