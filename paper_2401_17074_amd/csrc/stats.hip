@@ -20,49 +20,73 @@ namespace {
 
 constexpr int kStatBlock = 256;
 
-// Sum of v over the wave, in every lane, in a fixed order.
-__device__ __forceinline__ double wave_sum(double v) {
+// Sums of 16 values over the wave, in a fixed order: value lane / 4 in every
+// lane.  Each of the first four steps exchanges one half of the values a lane
+// still has against the other half of its partner's (17 exchanges in all,
+// where one value at a time takes 6 each).
+__device__ __forceinline__ double wave_sums(double (&v)[16]) {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int w = 32; w > 0; w >>= 1) v += __shfl_xor(v, w);
-    return v;
+    for (int h = 8; h > 0; h >>= 1) {
+        const bool upper = lane & (4 * h);
+#pragma unroll
+        for (int q = 0; q < h; ++q) {
+            const double keep = upper ? v[h + q] : v[q], give = upper ? v[q] : v[h + q];
+            v[q] = keep + __shfl_xor(give, 4 * h);
+        }
+    }
+    v[0] += __shfl_xor(v[0], 2);
+    return v[0] + __shfl_xor(v[0], 1);
 }
 
 // One plane's partial sums by one block.  A block's nodes are k, k + step, ...
 // of the plane (step = blocks_per_plane * kStatBlock), whose coordinates are
-// advanced instead of divided out.  What bounds it: the 12 bytes per node
-// read (384 x 192 x 192: 170 MB, 28 us at the copy rate); with 64-bit
-// divisions per node and a 13-value LDS tree for every four nodes of a thread
-// it took 68 us.
+// advanced instead of divided out, up to four at a time so that their loads
+// are in flight together.  What bounds it: the 12 bytes per node read (a
+// sample of 256^3 along y: 201 MB, 34 us at the copy rate, takes 40 us, 92 with
+// 64-bit divisions per node and a 13-value tree in LDS for every four nodes of
+// a thread); on small planes the block's reduction (64 x 4 x 4096 along z 18
+// us, 34 with one value reduced at a time, 20 with the tree).  Along x a block
+// reads one value of every row's cache lines; where one block does a plane,
+// neighbouring planes are given to one XCD, whose L2 keeps the lines for them
+// (2048 x 2048 55 us, 85 without; several blocks per plane share lines anyway:
+// 16 x 1000 x 200 32 us, 50 with it).
 template <class S>
 __global__ void __launch_bounds__(kStatBlock) profile_partial_kernel(const typename S::T* __restrict__ st,
                                                                      double* __restrict__ part, StepParams p,
                                                                      int axis, int blocks_per_plane) {
     const Geometry& g = p.geo;
-    const int j = blockIdx.y;
+    unsigned j = blockIdx.y;
+    if (axis == 0 && gridDim.x == 1) {
+        // blocks go round-robin to the 8 XCDs: a contiguous run of planes for each
+        j = (j & 7) * (gridDim.y >> 3) + (j >> 3);
+        if (j >= (unsigned)g.n[0]) return;
+    }
     const int d1 = axis == 0 ? 1 : 0, d2 = axis == 2 ? 1 : 2;
     const unsigned n1 = (unsigned)g.n[d1], n2 = (unsigned)g.n[d2];
-    const unsigned stride[3] = {1u, (unsigned)g.n[0], (unsigned)g.n[0] * (unsigned)g.n[1]};
-    double acc[13];
+    const unsigned row = (unsigned)g.n[0], slab = row * (unsigned)g.n[1];
+    const unsigned stride_j = axis == 0 ? 1u : axis == 1 ? row : slab, stride1 = axis == 0 ? row : 1u,
+                   stride2 = axis == 2 ? row : slab;
+    double acc[16];
 #pragma unroll
-    for (int q = 0; q < 13; ++q) acc[q] = 0.0;
+    for (int q = 0; q < 16; ++q) acc[q] = 0.0;
     const unsigned step = (unsigned)blocks_per_plane * kStatBlock, step1 = step % n1, step2 = step / n1;
-    const unsigned k0 = blockIdx.x * kStatBlock + threadIdx.x;
+    const unsigned first = blockIdx.x * kStatBlock, k0 = first + threadIdx.x;
     unsigned c1 = k0 % n1, c2 = k0 / n1;
     const bool plane_fluid = !(j == 0 && (((g.lo_solid | g.lo_ghost) >> axis) & 1)) &&
-                             !(j == g.n[axis] - 1 && (((g.hi_solid | g.hi_ghost) >> axis) & 1));
+                             !(j == (unsigned)g.n[axis] - 1 && (((g.hi_solid | g.hi_ghost) >> axis) & 1));
     const unsigned lo1 = ((g.lo_solid | g.lo_ghost) >> d1) & 1, hi1 = n1 - (((g.hi_solid | g.hi_ghost) >> d1) & 1);
     const unsigned lo2 = ((g.lo_solid | g.lo_ghost) >> d2) & 1, hi2 = n2 - (((g.hi_solid | g.hi_ghost) >> d2) & 1);
     const auto* __restrict__ u0p = st + 1 * g.N;
     const auto* __restrict__ u1p = st + 2 * g.N;
     const auto* __restrict__ u2p = st + 3 * g.N;
-    while (plane_fluid && c2 < n2) {
-        // four nodes at a time, so that their loads are in flight together
-        typename S::T r[4][3];
-        bool on[4];
+    auto nodes = [&]<int E>() {
+        typename S::T r[E][3];
+        bool on[E];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            on[e] = c2 < n2 && c1 >= lo1 && c1 < hi1 && c2 >= lo2 && c2 < hi2;
-            const unsigned n = on[e] ? (unsigned)j * stride[axis] + c1 * stride[d1] + c2 * stride[d2] : 0u;
+        for (int e = 0; e < E; ++e) {
+            on[e] = c1 >= lo1 && c1 < hi1 && c2 >= lo2 && c2 < hi2;
+            const unsigned n = on[e] ? j * stride_j + c1 * stride1 + c2 * stride2 : 0u;
             r[e][0] = u0p[n];
             r[e][1] = u1p[n];
             r[e][2] = u2p[n];
@@ -74,7 +98,7 @@ __global__ void __launch_bounds__(kStatBlock) profile_partial_kernel(const typen
             }
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < E; ++e) {
             if (!on[e]) continue;
             const double u0 = S::load(r[e][0], p.inv_scale[1]);
             const double u1 = S::load(r[e][1], p.inv_scale[1]);
@@ -93,14 +117,17 @@ __global__ void __launch_bounds__(kStatBlock) profile_partial_kernel(const typen
             acc[11] += u1 * u1 * u1;
             acc[12] += u2 * u2 * u2;
         }
-    }
+    };
+    // nodes of the block's first thread, at least as many as any other's
+    const unsigned plane = n1 * n2;
+    unsigned left = plane_fluid && first < plane ? (plane - first + step - 1) / step : 0;
+    for (; left >= 4; left -= 4) nodes.template operator()<4>();
+    if (left & 2) nodes.template operator()<2>();
+    if (left & 1) nodes.template operator()<1>();
     // block reduction in a fixed order: within each wave, then over the waves
-    __shared__ double red[kStatBlock / 64][13];
-#pragma unroll
-    for (int q = 0; q < 13; ++q) {
-        const double v = wave_sum(acc[q]);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = v;
-    }
+    __shared__ double red[kStatBlock / 64][16];
+    const double sum = wave_sums(acc);
+    if ((threadIdx.x & 3) == 0) red[threadIdx.x >> 6][(threadIdx.x & 63) >> 2] = sum;
     __syncthreads();
     if (threadIdx.x < 13) {
         double v = red[0][threadIdx.x];
@@ -114,14 +141,17 @@ __global__ void __launch_bounds__(kStatBlock) profile_partial_kernel(const typen
 // side by side, added in a fixed order (one thread per value, 64 partials one
 // after the other, took 20 us).
 __global__ void __launch_bounds__(64) profile_final_kernel(const double* __restrict__ part, double* __restrict__ sums,
-                                                           int blocks_per_plane) {
-    const int j = blockIdx.x, q = threadIdx.x & 15;
-    double s = 0.0;
-    if (q < 13)
-        for (int b = threadIdx.x >> 4; b < blocks_per_plane; b += 4) s += part[((long long)j * blocks_per_plane + b) * 13 + q];
-    s += __shfl_xor(s, 16);
-    s += __shfl_xor(s, 32);
-    if (threadIdx.x < 13) sums[(long long)j * 13 + q] += s;
+                                                           int n_axis, int blocks_per_plane) {
+    const int q = threadIdx.x & 15;
+    for (int j = blockIdx.x; j < n_axis; j += gridDim.x) {
+        double s = 0.0;
+        if (q < 13)
+            for (int b = threadIdx.x >> 4; b < blocks_per_plane; b += 4)
+                s += part[((long long)j * blocks_per_plane + b) * 13 + q];
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        if (threadIdx.x < 13) sums[(long long)j * 13 + q] += s;
+    }
 }
 
 template <class S>
@@ -242,11 +272,12 @@ template <class S>
 hipError_t profile_s(const void* st, double* part, double* sums, const StepParams& p, int axis, int bpp,
                      hipStream_t s) {
     const int n_axis = p.geo.n[axis];
-    hipLaunchKernelGGL(profile_partial_kernel<S>, dim3(bpp, n_axis), dim3(kStatBlock), 0, s,
+    const unsigned planes = axis == 0 && bpp == 1 ? ((unsigned)n_axis + 7u) & ~7u : (unsigned)n_axis;  // whole runs per XCD
+    hipLaunchKernelGGL(profile_partial_kernel<S>, dim3(bpp, planes), dim3(kStatBlock), 0, s,
                        (const typename S::T*)st, part, p, axis, bpp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(profile_final_kernel, dim3(n_axis), dim3(64), 0, s, part, sums, bpp);
+    hipLaunchKernelGGL(profile_final_kernel, dim3(std::min(n_axis, 1 << 20)), dim3(64), 0, s, part, sums, n_axis, bpp);
     return hipGetLastError();
 }
 
