@@ -628,7 +628,7 @@ int tslb_load_state(tslb_handle h, const void* src, void* stream) {
     HIP_TRY(hipMemcpyAsync(h->buf[h->cur], src, tslb_state_bytes(h), hipMemcpyDeviceToDevice, S(stream)));
     // the other buffer takes what no step writes: wall nodes, z components
     if ((h->p.geo.lo_solid | h->p.geo.hi_solid) != 0 || h->p.dims == 2)
-        HIP_TRY(launch_copy_state(h->buf[1 - h->cur], h->buf[h->cur], tslb_state_bytes(h), S(stream)));
+        HIP_TRY(hipMemcpyAsync(h->buf[1 - h->cur], src, tslb_state_bytes(h), hipMemcpyDeviceToDevice, S(stream)));
     return TSLB_OK;
 }
 
