@@ -379,18 +379,26 @@ __global__ void __launch_bounds__(kD2Block) update_d2q9_kernel(const Fields2<typ
 
 // Spans and segments.  The chip takes 4096 wavefronts at 16 per CU; rows per
 // segment so that there are as many, down to one row: at least three rows of
-// loads in a chain (256 x 256: 5.2 us; with segments of 16 rows 18.6).
+// loads in a chain (256 x 256: 5.2 us; with segments of 16 rows 18.6).  Up to
+// four rows in all are not cut where the spans alone give each CU four
+// wavefronts: a cut costs two rows of halo (100000 x 3: 8.3 us, 11.4 cut).
 // Two columns per lane where that still leaves segments of eight rows (8192 x
-// 4096: 320 us, 343 with one column; 512 x 512 7.0 and 6.8).  FP32, bound by
-// memory, takes up to 32 rows at eight wavefronts per CU instead, for fewer
-// halo rows (4096 x 2048: 82.4 us with 32 rows, 85.2 with 16); 16-bit storage,
-// bound by arithmetic, does not (2048 x 2048 FP16: 28.6 us with 8 rows, 33.0
-// with 16).
+// 4096: 320 us, 343 with one column; 512 x 512 7.0 and 6.8) or, of up to four
+// rows, 4096 wavefronts (2^22 x 2: 100 and 110), and at most a ninth of the
+// columns more (3 x 100000: 38 us with one column, 64 with two;
+// 64 x 65536 36 and 49).  FP32, bound by memory, takes up to 32 rows at eight
+// wavefronts per CU instead, for fewer halo rows (4096 x 2048: 82.4 us with 32
+// rows, 85.2 with 16), but no number between (128 x 100000: 133 us with 25
+// rows, 162 with 32, which give three blocks to some CUs and four to others);
+// 16-bit storage, bound by arithmetic, does not (2048 x 2048 FP16: 28.6 us
+// with 8 rows, 33.0 with 16).
 template <class S, int ORDER, bool FIELD, bool NT>
 hipError_t launch_c(const Fields2<typename S::T>& f, const StepParams& p, hipStream_t s) {
     const int nx = p.geo.n[0], ny = p.geo.n[1];
     constexpr long long kWaves = 4096;
-    auto rows = [&](int spans) { return (int)std::max(1LL, ((long long)ny * spans + kWaves - 1) / kWaves); };
+    auto rows = [&](int spans) {
+        return ny <= 4 && spans >= kWaves / 4 ? ny : (int)std::max(1LL, ((long long)ny * spans + kWaves - 1) / kWaves);
+    };
     auto run = [&]<int C>(int seg_rows) {
         const int spans = (nx + 64 * C - 1) / (64 * C), segments = (ny + seg_rows - 1) / seg_rows;
         const long long waves = (long long)spans * segments;
@@ -400,9 +408,10 @@ hipError_t launch_c(const Fields2<typename S::T>& f, const StepParams& p, hipStr
                            segments, seg_rows);
         return hipGetLastError();
     };
-    const int r2 = rows((nx + 127) / 128);
-    if (r2 < 8) return run.template operator()<1>(rows((nx + 63) / 64));
-    return run.template operator()<2>(sizeof(typename S::T) == 4 ? std::max(r2, std::min(32, 2 * r2)) : r2);
+    const int one = (nx + 63) / 64, two = (nx + 127) / 128, r2 = rows(two);
+    const bool full = r2 >= 8 || (ny <= 4 && two >= kWaves);
+    if (!full || 9 * (2 * two - one) > one) return run.template operator()<1>(rows(one));
+    return run.template operator()<2>(sizeof(typename S::T) == 4 && r2 <= 16 ? 2 * r2 : r2);
 }
 
 template <class S, int ORDER>
