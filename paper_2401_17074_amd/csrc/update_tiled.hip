@@ -31,13 +31,15 @@ int tiled_columns_rows13_bf16(const Geometry& g);
 // 17.8 (9), 96^3 18.2 (8) / 20.4 (11); adjoint step of 64^3 11.5 / 10.5).
 // 16-bit storage, 13 rows: a block has 16 waves in place of 15, so fewer halo
 // columns per node, but no SIMD with a wave less.  Taken where two levels
-// exceed the Infinity Cache (us per step, 12 rows / 13, channel FP16: 512 x 256
-// x 256 393 / 383, 384 x 192 x 192 180 / 175, 333 x 210 x 140 141 / 138; below,
-// 128^3 30.7 / 33.5, 249 x 166 x 108 63.7 / 66.6; FP32, bound by memory, keeps
-// 12: 512 x 256 x 256 538 / 557), or where they exceed L2 and 13 rows save 15 %
-// of the plane-steps (200 x 150 x 100 52.1 / 51.0; jet 160 x 64 x 320 BF16 77.2
-// / 72.2).  Levels that fit L2 keep 12.  The values do not depend on
-// the height (see crosses_up).
+// exceed the Infinity Cache, with walls always (us per step, 12 rows / 13, FP16:
+// channels 512 x 256 x 256 386 / 389, 384 x 192 x 192 179 / 179, 512 x 96 x 400
+// 255 / 240, 250^3 216 / 203), without where they save a fifteenth of the
+// plane-steps (389 x 386 x 86 224 / 205, 96 x 160 x 736 314 / 296; not 512 x 96
+// x 400 216 / 228, 160 x 200 x 210 87 / 96, 864 x 120 x 175 237 / 250); or where
+// they exceed L2 and 13 rows save 15 % of the plane-steps (200 x 150 x 100 50.4
+// / 48.4, jet 160 x 64 x 320 BF16 76.4 / 70.4; not 128^3 30.7 / 33.5).  FP32,
+// bound by memory, keeps 12 (512 x 256 x 256 538 / 557).  Levels that fit L2
+// keep 12.  The values do not depend on the height (see crosses_up).
 hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg, int& grid, int& nseg, int& other_rows,
                           long long& steps) {
     const int resident = (compute_units() + 7) & ~7;  // one block per CU
@@ -46,6 +48,7 @@ hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg
                       : storage == 1 ? tiled_columns_rows13_f16(g)
                                      : tiled_columns_rows13_bf16(g);
     Schedule s;
+    other_rows = 0;
     if (storage == 0) {
         s = build_schedule(columns, g.n[2], resident);
         steps = s.cost;
@@ -54,10 +57,11 @@ hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg
         if (other_rows) s = std::move(s8);
     } else {
         const size_t levels = 2 * 20 * (size_t)g.N;
-        other_rows = levels > kInfinityCacheBytes;
-        s = build_schedule(other_rows ? other : columns, g.n[2], resident);
-        if (!other_rows && levels > kL2Bytes) {
-            Schedule s13 = build_schedule(other, g.n[2], resident, 17 * s.cost / 20);
+        s = build_schedule(columns, g.n[2], resident);
+        if (levels > kL2Bytes) {
+            const bool walls = (g.lo_solid | g.hi_solid) != 0;
+            const long long most = levels <= kInfinityCacheBytes ? 17 * s.cost / 20 : walls ? -1 : 14 * s.cost / 15;
+            Schedule s13 = build_schedule(other, g.n[2], resident, most);
             other_rows = s13.grid > 0;
             if (other_rows) s = std::move(s13);
         }

@@ -115,7 +115,7 @@ __device__ __forceinline__ const float (&arrived(const raw_t<S> (&r)[10], const 
 // a template parameter since the compiler merges a branch between the two
 // kinds into plain stores (4 % slower on the FP32 channels).  XGHOST: grids
 // with x ghost faces, whose fluid neighbours also write those ghost nodes.
-template <class S, bool WALLS, bool FIELD, int ORDER, int LAT, bool NT, bool XGHOST>
+template <class S, bool WALLS, bool FIELD, int ORDER, int LAT, bool NT, bool XGHOST, bool LATE>
 __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
     update_tiled_kernel(const char* __restrict__ in, char* __restrict__ out, StepParams p, int tiles_x) {
     static_assert(TX == 64 && 4 + 2 * TY <= 64 && NTHREADS == NINT + 192, "one wave per row, three halo waves");
@@ -126,14 +126,12 @@ __global__ void __launch_bounds__(NTHREADS, TSLB_WAVES_PER_EU)
     // D3Q27: the populations travel without their weights, which the gather
     // applies for free (add_slice); D3Q19's weights are not separable
     constexpr bool kDeferWeights = LAT == 27;
-    // How far loads run ahead.  FP32, rows of whole cache lines: two
-    // plane-steps, in two register sets used in turn (kTwo).  FP32, other
-    // rows: one (kOne); there tiles share lines and two planes of all blocks
-    // of an XCD (3.7 MB) push the halves of stored lines out of its L2 before
-    // the neighbour completes them (333 x 101 x 77 45.0 against 44.5 us,
-    // 181 x 428 x 145 220 against 212 us).  16-bit: one set, converted out of
-    // as it arrives and reloaded at once, a whole plane-step ahead.
-    constexpr bool kTwo = kSize == 4 && NT, kOne = kSize == 4 && !NT;
+    // How far loads run ahead.  FP32 with non-temporal stores: two plane-steps,
+    // in two register sets used in turn (kTwo).  LATE: to the next plane, with
+    // this one's exchange (see loads_late).  Else, 16-bit: one set, converted
+    // out of as it arrives and reloaded at once, a whole plane-step ahead.
+    constexpr bool kTwo = kSize == 4 && NT, kOne = LATE;
+    static_assert(kSize == 2 || NT != LATE);
     // Tiles whose rows are not the frame's (see crosses_up): the rows on both
     // sides of a border of the frame evaluate one slice twice, the halo rows
     // elsewhere theirs in full.  Halo rows collapsed at every tile border were
@@ -603,12 +601,12 @@ bool writes_x_ghosts(const StepParams& p) {
     return x_ghost_faces(p) && (p.geo.lo_solid | p.geo.hi_solid) == 0 && p.gfield == nullptr && rows_whole_lines<S>(p);
 }
 
-template <class S, bool WALLS, bool FIELD, int ORDER, int LAT, bool NT, bool XGHOST>
+template <class S, bool WALLS, bool FIELD, int ORDER, int LAT, bool NT, bool XGHOST, bool LATE = sizeof(typename S::T) == 4 && !NT>
 hipError_t launch_k(const void* in, void* out, const StepParams& p, hipStream_t s) {
     if (p.geo.N >= (1LL << 30)) return hipErrorInvalidValue;  // 32-bit byte offsets
     if (!p.sched || p.sched_grid < 8 || p.sched_nseg < 1) return hipErrorInvalidValue;
     const int tiles_x = (p.geo.n[0] + TX - 1) / TX;
-    hipLaunchKernelGGL((update_tiled_kernel<S, WALLS, FIELD, ORDER, LAT, NT, XGHOST>), dim3(p.sched_grid),
+    hipLaunchKernelGGL((update_tiled_kernel<S, WALLS, FIELD, ORDER, LAT, NT, XGHOST, LATE>), dim3(p.sched_grid),
                        dim3(NTHREADS), 0, s, (const char*)in, (char*)out, p, tiles_x);
     return hipGetLastError();
 }
@@ -627,6 +625,21 @@ bool streams_out(const StepParams& p) {
     return rows_whole_lines<S>(p) && (kSize == 2 || 20 * kSize * (size_t)p.geo.N > kInfinityCacheBytes);
 }
 
+// Loads with the exchange (LATE)?  Where tiles share lines, two planes of all
+// blocks of an XCD push the halves of stored lines out of its L2 before the
+// neighbour completes them, so the loads run ahead less: FP32 on every such
+// grid (us, two planes ahead / late: 333 x 101 x 77 45.0 / 44.5, 181 x 428 x
+// 145 220 / 212), 16-bit storage in tiles of 12 rows without
+// a force field where two levels stay about in the Infinity Cache (us, late /
+// a plane ahead: 110 x 131 x 313 FP16 61.4 / 64.8, 271 x 271 x 39 44.1 / 46.5,
+// 160 x 200 x 210, 269 MB, 86.5 / 89.2, 77 x 300 x 300, 277 MB, 124.3 / 126.3;
+// beyond, 129 x 400 x 140, 289 MB, 124.7 / 121.1, 250^3 203.5 / 196.1; with a
+// field 160 x 992 x 32 70.9 / 66.5; 13 rows 333 x 210 x 140 143.6 / 137).
+template <class S>
+bool loads_late(const StepParams& p) {
+    return !rows_whole_lines<S>(p) && 40 * (size_t)p.geo.N <= kInfinityCacheBytes / 20 * 21;
+}
+
 template <class S, bool WALLS, bool FIELD, int ORDER, int LAT>
 hipError_t launch_t(const void* in, void* out, const StepParams& p, hipStream_t s) {
     const bool nt = streams_out<S>(p);
@@ -637,6 +650,8 @@ hipError_t launch_t(const void* in, void* out, const StepParams& p, hipStream_t 
             return launch_k<S, false, false, ORDER, LAT, true, true>(in, out, p, s);
         }
     if (nt) return launch_k<S, WALLS, FIELD, ORDER, LAT, true, false>(in, out, p, s);
+    if constexpr (sizeof(typename S::T) == 2 && TY == kFrameY && !FIELD)
+        if (loads_late<S>(p)) return launch_k<S, WALLS, FIELD, ORDER, LAT, false, false, true>(in, out, p, s);
     return launch_k<S, WALLS, FIELD, ORDER, LAT, false, false>(in, out, p, s);
 }
 
