@@ -181,12 +181,15 @@ def tslb_stats_profile(h, n_axis, stream=None):
     return [list(buf[13 * j:13 * j + 13]) for j in range(n_axis)], ns.value
 
 
-def tslb_stats_profile_into(h, sums, stream=None):
+def tslb_stats_profile_into(h, sums, n_axis, stream=None):
     """tslb_stats_profile into a contiguous float64 host tensor of 13 n_axis
-    values; returns the number of samples."""
+    values (n_axis: nodes along the profile axis); returns the number of
+    samples."""
+    import torch
+    if sums.device.type != "cpu" or sums.dtype != torch.float64 or sums.numel() != 13 * n_axis:
+        raise ValueError("sums must be %d float64 values on the host" % (13 * n_axis))
     ns = ctypes.c_int64()
-    _check(lib.tslb_stats_profile(h, ctypes.cast(sums.data_ptr(), ctypes.POINTER(_d)), ctypes.byref(ns),
-                                  _stream(stream)))
+    _check(lib.tslb_stats_profile(h, ctypes.cast(_ptr(sums), ctypes.POINTER(_d)), ctypes.byref(ns), _stream(stream)))
     return ns.value
 
 

@@ -85,11 +85,12 @@ class Solver:
         C.tslb_stats_sample(self.h)
 
     def stats_profile(self):
-        """(sums (n_axis, 13) float64 tensor on the host, number of samples)."""
+        """(sums (n_axis, 13) float64 tensor on the default device, which is
+        the host unless set otherwise, number of samples)."""
         n_axis = (self.shape[2], self.shape[1], self.shape[0])[self._stats_axis]
-        rows = torch.empty((n_axis, 13), dtype=torch.float64)
-        ns = C.tslb_stats_profile_into(self.h, rows)
-        return rows, ns
+        rows = torch.empty((n_axis, 13), dtype=torch.float64, device="cpu")
+        ns = C.tslb_stats_profile_into(self.h, rows, n_axis)
+        return rows.to(torch.get_default_device()), ns
 
     def stats_field(self):
         """Per-node mean velocity (3, nz, ny, nx) and covariances (6, ...)."""
