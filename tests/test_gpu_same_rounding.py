@@ -66,7 +66,7 @@ def test_other_orders_and_lattice(dims, copies, order, lattice):
 @pytest.mark.parametrize("nx", [64, 65])
 @pytest.mark.parametrize("faces", sorted(XY))
 def test_16_bit_tiles_of_13_rows_as_12(kind, nx, faces):
-    _check((nx, 40, 26), 104, XY[faces], kind=kind)
+    _check((nx, 39, 26), 104, XY[faces], kind=kind)
 
 
 def rollout_loss(dims, steps, every):
