@@ -1,4 +1,4 @@
-// Brick update kernel for gfx950: the update of small grids.
+// Brick update kernel for gfx950: the FP32 update of small and narrow grids.
 //
 // The tiled update marches 64 x 12 columns along z, a plane per step; on a
 // grid of a few hundred thousand nodes most of its time is the chain of those
@@ -9,7 +9,7 @@
 // publishes them in LDS, and after one barrier the four waves gather the
 // arriving values of their nodes, sum and store.  One load latency, one
 // exchange, no serial chain; the price is 648 nodes built for 256 updated,
-// which is why the marching kernel takes over on larger grids (see
+// which is why the marching kernel takes over on larger and wider grids (see
 // prefers_brick).
 #include "tslb_tiles.h"
 
@@ -37,16 +37,14 @@ __device__ __forceinline__ int brick_index(int v, int n, bool periodic) {
     return v;
 }
 
-template <class S, bool WALLS, int ORDER, int LAT>
+template <bool WALLS, int ORDER, int LAT>
 __global__ void __launch_bounds__(kBrickThreads, 6)
-    update_brick_kernel(const char* __restrict__ in, char* __restrict__ out, StepParams p, int bricks_x, int bricks_y,
+    update_brick_kernel(const float* __restrict__ in, float* __restrict__ out, StepParams p, int bricks_x, int bricks_y,
                         int bricks) {
-    using T = typename S::T;
-    constexpr unsigned kSize = sizeof(T);
     constexpr bool kDeferWeights = LAT == 27;
     __shared__ float lds[27][kBrickNodes];
     const Geometry& g = p.geo;
-    const size_t stride = (size_t)g.N * kSize;
+    const size_t stride = (size_t)g.N * 4;
     // each XCD takes a contiguous run of bricks (block ids go round-robin)
     const int per = (int)(gridDim.x >> 3);
     const int b = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
@@ -102,11 +100,11 @@ __global__ void __launch_bounds__(kBrickThreads, 6)
         const int wy = brick_index(y, g.n[1], g.periodic & 2);
         const int wz = brick_index(z, g.n[2], g.periodic & 4);
         const unsigned n = (unsigned)wx + (unsigned)g.n[0] * ((unsigned)wy + (unsigned)g.n[1] * (unsigned)wz);
-        T r[10];
-        FieldAddress f(in, n * kSize);
+        float m[10];
+        FieldAddress f(in, n * 4u);
 #pragma unroll
         for (int q = 0; q < 10; ++q) {
-            r[q] = __builtin_bit_cast(T, *f.template lane<const store_bits<T>>());
+            m[q] = *f.template lane<const float>();
             f.next(stride);
         }
         float gl[3] = {p.force[0], p.force[1], p.force[2]};
@@ -116,16 +114,8 @@ __global__ void __launch_bounds__(kBrickThreads, 6)
         }
         // wall nodes emit nothing: they hold the rest state, and no force
         if (WALLS && is_solid(g, wx, wy, wz)) gl[0] = gl[1] = gl[2] = 0.0f;
-        float m[10];
-        m[0] = S::load(r[0], p.inv_scale[0]);
-#pragma unroll
-        for (int q = 1; q < 4; ++q) m[q] = S::load(r[q], p.inv_scale[1]);
-#pragma unroll
-        for (int q = 4; q < 10; ++q) m[q] = S::convert(r[q]);
-        // 1 - omega takes the stored Pi^neq scale
-        const float omo = omo_at(p, wz);
         float A[NK];
-        coefficients<ORDER, LAT>(m, gl, kSize == 4 ? omo : omo * p.inv_scale[2], A);
+        coefficients<ORDER, LAT>(m, gl, omo_at(p, wz), A);
         float* const w = &lds[0][own];
         if constexpr (LAT == 19) {
             // evaluated in full by every node, as in the tiled update
@@ -210,36 +200,29 @@ __global__ void __launch_bounds__(kBrickThreads, 6)
     float o[10];
     finalize<LAT == 19 ? 36 : 216>(a, o);
     const unsigned n = (unsigned)x + (unsigned)g.n[0] * ((unsigned)y + (unsigned)g.n[1] * (unsigned)z);
-    FieldAddress f(out, n * kSize);
+    FieldAddress f(out, n * 4u);
 #pragma unroll
     for (int q = 0; q < 10; ++q) {
-        *f.template lane<store_bits<T>>() =
-            __builtin_bit_cast(store_bits<T>, S::store(o[q], p.scale[q == 0 ? 0 : q < 4 ? 1 : 2]));
+        *f.template lane<float>() = o[q];
         f.next(stride);
     }
 }
 
-template <class S, bool WALLS, int ORDER, int LAT>
-hipError_t launch_k(const void* in, void* out, const StepParams& p, hipStream_t s) {
+template <bool WALLS, int ORDER, int LAT>
+hipError_t launch_k(const float* in, float* out, const StepParams& p, hipStream_t s) {
     const int bx = (p.geo.n[0] + BX - 1) / BX, by = (p.geo.n[1] + BY - 1) / BY;
     const long long bricks = brick_count(p.geo);
     if (p.geo.N >= (1LL << 30) || bricks > kMaxBricks) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)((bricks + 7) & ~7LL);  // whole runs per XCD
-    hipLaunchKernelGGL((update_brick_kernel<S, WALLS, ORDER, LAT>), dim3(grid), dim3(kBrickThreads), 0, s,
-                       (const char*)in, (char*)out, p, bx, by, (int)bricks);
+    hipLaunchKernelGGL((update_brick_kernel<WALLS, ORDER, LAT>), dim3(grid), dim3(kBrickThreads), 0, s, in, out, p, bx, by,
+                       (int)bricks);
     return hipGetLastError();
 }
 
-template <class S, int ORDER, int LAT>
-hipError_t launch_w(const void* in, void* out, const StepParams& p, hipStream_t s) {
-    return (p.geo.lo_solid | p.geo.hi_solid) != 0 ? launch_k<S, true, ORDER, LAT>(in, out, p, s)
-                                                  : launch_k<S, false, ORDER, LAT>(in, out, p, s);
-}
-
-template <class S>
-hipError_t launch_s(const void* in, void* out, const StepParams& p, hipStream_t s) {
-    if (p.lattice == 19) return p.order == 2 ? launch_w<S, 2, 19>(in, out, p, s) : launch_w<S, 3, 19>(in, out, p, s);
-    return p.order == 2 ? launch_w<S, 2, 27>(in, out, p, s) : launch_w<S, 3, 27>(in, out, p, s);
+template <int ORDER, int LAT>
+hipError_t launch_w(const float* in, float* out, const StepParams& p, hipStream_t s) {
+    return (p.geo.lo_solid | p.geo.hi_solid) != 0 ? launch_k<true, ORDER, LAT>(in, out, p, s)
+                                                  : launch_k<false, ORDER, LAT>(in, out, p, s);
 }
 
 }  // namespace
@@ -264,8 +247,11 @@ bool prefers_brick(int storage, const Geometry& g, long long steps, bool rows8) 
     return brick_grid(storage, g, steps, rows8, compute_units());
 }
 
-hipError_t launch_update_brick(const void* in, void* out, const StepParams& p, hipStream_t s) {
-    return launch_s<StoreF32>(in, out, p, s);
+hipError_t launch_update_brick(const void* in_, void* out_, const StepParams& p, hipStream_t s) {
+    const float* in = (const float*)in_;
+    float* out = (float*)out_;
+    if (p.lattice == 19) return p.order == 2 ? launch_w<2, 19>(in, out, p, s) : launch_w<3, 19>(in, out, p, s);
+    return p.order == 2 ? launch_w<2, 27>(in, out, p, s) : launch_w<3, 27>(in, out, p, s);
 }
 
 }  // namespace tslb
