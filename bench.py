@@ -35,9 +35,12 @@ VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
 BYTES_PER_FIELD = {0: 4, 1: 2, 2: 2}
 
 
-# the sources the tiled update kernel is compiled from: HBM counters taken
-# with other sources are not reported as this kernel's traffic
-KERNEL_SOURCES = ("update_tiled_kernel.h", "update_tiled.hip", "tslb_tiles.h", "tslb_device.h", "tslb_params.h")
+# the sources the tiled update kernel and its choice of tiles are compiled
+# from: HBM counters taken with other sources are not reported as this
+# kernel's traffic
+KERNEL_SOURCES = ("update_tiled_kernel.h", "update_tiled.hip", "update_tiled_f32.hip", "update_tiled_f16.hip",
+                  "update_tiled_bf16.hip", "update_tiled_rows8_f32.hip", "update_tiled_rows13_f16.hip",
+                  "update_tiled_rows13_bf16.hip", "tslb_tiles.h", "tslb_device.h", "tslb_params.h", "tslb_internal.h")
 
 
 def _source_hash():

@@ -713,7 +713,8 @@ int tslb_rollout_backward(tslb_handle h, int nsteps, int every, void* ws, size_t
         const int len = (nsteps - s0 < every) ? nsteps - s0 : every;
         // recompute the segment once from its checkpoint (its level 0), each
         // level straight into its slot (the handle's own buffers are not
-        // touched)
+        // touched; the slot of level 0 is spare, the workspace has the size
+        // that tslb_rollout_workspace_bytes has always given)
         auto level = [&](int k) { return k == 0 ? ck + (size_t)seg * sb : seg_states + (size_t)k * sb; };
         for (int k = 1; k <= len; ++k) {
             h->t = t_end - nsteps + s0 + k - 1;

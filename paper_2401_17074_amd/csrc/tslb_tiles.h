@@ -384,51 +384,56 @@ struct Schedule {
 };
 
 // The schedule for one (tz, split); with build == false only its cost (the
-// largest per-block sum of L + 2 over the block's segments) and shape.
-inline Schedule schedule_for(int columns, int nz, int resident, int tz, int split, bool build) {
+// largest per-block sum of L + 2 over the block's segments) and shape, given up
+// as soon as the cost exceeds `most`.
+inline Schedule schedule_for(int columns, int nz, int resident, int tz, int split, bool build,
+                             long long most = 1LL << 62) {
     const int tiles_z = (nz + tz - 1) / tz;
-    const long long ntiles = (long long)columns * tiles_z;
+    const int ntiles = columns * tiles_z;  // no more than nodes, < 2^30
     const int nb = resident;  // a multiple of 8
-    const long long rounds = ntiles / nb;
-    std::vector<long long> cost(nb, 0);
-    std::vector<int> count(nb, 0);
+    const int rounds = ntiles / nb;
+    // the first whole rounds, all of tiles of tz planes, cost every block the
+    // same: only counted unless the list is wanted
+    const int equal = build ? 0 : std::min(rounds, columns * (nz / tz) / nb);
+    std::vector<long long> cost(nb, (long long)equal * (tz + 2));
+    std::vector<int> count(nb, equal);
     std::vector<std::vector<int4>> lists(build ? nb : 0);
     // item i of a round of n items: XCD i / per, slot i % per, per = n / 8
     // rounded up, so every XCD takes a contiguous run of the round's items
-    auto deal = [&](long long i, long long n, int col, int z0, int z1) {
-        const long long per = (n + 7) / 8;
-        const long long b = 8 * (i % per) + i / per;
+    auto deal = [&](int i, int n, int col, int z0, int z1) {
+        const int per = (n + 7) / 8, b = 8 * (i % per) + i / per;
         cost[b] += z1 - z0 + 2;
         count[b] += 1;
         if (build) lists[b].push_back(make_int4(col, z0, z1, 0));
+        return cost[b] <= most;
     };
-    auto tile = [&](long long t, int& col, int& z0, int& z1) {
-        col = (int)(t % columns);
-        z0 = (int)(t / columns) * tz;
-        z1 = std::min(z0 + tz, nz);
-    };
-    for (long long t = 0; t < rounds * nb; ++t) {
-        int col, z0, z1;
-        tile(t, col, z0, z1);
-        deal(t % nb, nb, col, z0, z1);
-    }
-    // leftover tiles, each cut into `split` parts along z (part index major)
-    const long long left = ntiles - rounds * nb;
-    const long long parts = left * split;
-    for (long long q = 0; q < parts; ++q) {
-        const long long t = rounds * nb + q % left;
-        const int k = (int)(q / left);
-        int col, z0, z1;
-        tile(t, col, z0, z1);
-        const int len = z1 - z0;
-        const int a = z0 + (int)((long long)len * k / split), e = z0 + (int)((long long)len * (k + 1) / split);
-        if (a == e) continue;  // a part of a short tile may be empty
-        const long long r0 = q / nb * nb;
-        deal(q - r0, std::min<long long>(nb, parts - r0), col, a, e);
-    }
     Schedule s;
     s.tz = tz;
     s.split = split;
+    s.cost = most + 1;
+    auto tile = [&](int t, int& col, int& z0, int& z1) {
+        col = t % columns;
+        z0 = t / columns * tz;
+        z1 = std::min(z0 + tz, nz);
+    };
+    for (int t = equal * nb; t < rounds * nb; ++t) {
+        int col, z0, z1;
+        tile(t, col, z0, z1);
+        if (!deal(t % nb, nb, col, z0, z1)) return s;
+    }
+    // leftover tiles, each cut into `split` parts along z (part index major)
+    const int left = ntiles - rounds * nb, parts = left * split;
+    for (int q = 0; q < parts; ++q) {
+        const int t = rounds * nb + q % left, k = q / left;
+        int col, z0, z1;
+        tile(t, col, z0, z1);
+        const int len = z1 - z0;
+        const int a = z0 + len * k / split, e = z0 + len * (k + 1) / split;
+        if (a == e) continue;  // a part of a short tile may be empty
+        const int r0 = q / nb * nb;
+        if (!deal(q - r0, std::min(nb, parts - r0), col, a, e)) return s;
+    }
+    s.cost = 0;
     int last = -1;
     for (int b = 0; b < nb; ++b) {
         s.cost = std::max(s.cost, cost[b]);
@@ -462,7 +467,7 @@ inline Schedule build_schedule(int columns, int nz, int resident, long long limi
         if (mean > bound) continue;
         for (int split = left ? std::min(tz, 8) : 1; split >= 1; --split) {
             if ((tiles >= resident ? tz : (tz + split - 1) / split) + 2 > bound) continue;
-            const Schedule s = schedule_for(columns, nz, resident, tz, split, false);
+            const Schedule s = schedule_for(columns, nz, resident, tz, split, false, bound);
             if (s.cost > bound) continue;
             bound = s.cost;
             // visited from the largest (tz, split) down: of equals the last stays

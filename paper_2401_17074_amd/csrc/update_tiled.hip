@@ -34,7 +34,7 @@ int tiled_columns_rows13_bf16(const Geometry& g);
 // exceed the Infinity Cache, with walls always (us per step, 12 rows / 13, FP16:
 // channels 512 x 256 x 256 386 / 389, 384 x 192 x 192 179 / 179, 512 x 96 x 400
 // 255 / 240, 250^3 216 / 203), without where they save a fifteenth of the
-// plane-steps (389 x 386 x 86 224 / 205, 96 x 160 x 736 314 / 296; not 512 x 96
+// tile columns (389 x 386 x 86 224 / 205, 96 x 160 x 736 314 / 296; not 512 x 96
 // x 400 216 / 228, 160 x 200 x 210 87 / 96, 864 x 120 x 175 237 / 250); or where
 // they exceed L2 and 13 rows save 15 % of the plane-steps (200 x 150 x 100 50.4
 // / 48.4, jet 160 x 64 x 320 BF16 76.4 / 70.4; not 128^3 30.7 / 33.5).  FP32,
@@ -57,11 +57,11 @@ hipError_t tiled_schedule(int storage, const Geometry& g, std::vector<int4>& seg
         if (other_rows) s = std::move(s8);
     } else {
         const size_t levels = 2 * 20 * (size_t)g.N;
-        s = build_schedule(columns, g.n[2], resident);
-        if (levels > kL2Bytes) {
-            const bool walls = (g.lo_solid | g.hi_solid) != 0;
-            const long long most = levels <= kInfinityCacheBytes ? 17 * s.cost / 20 : walls ? -1 : 14 * s.cost / 15;
-            Schedule s13 = build_schedule(other, g.n[2], resident, most);
+        const bool walls = (g.lo_solid | g.hi_solid) != 0;
+        other_rows = levels > kInfinityCacheBytes && (walls || 15LL * other <= 14LL * columns);
+        s = build_schedule(other_rows ? other : columns, g.n[2], resident);
+        if (levels > kL2Bytes && levels <= kInfinityCacheBytes) {
+            Schedule s13 = build_schedule(other, g.n[2], resident, 17 * s.cost / 20);
             other_rows = s13.grid > 0;
             if (other_rows) s = std::move(s13);
         }

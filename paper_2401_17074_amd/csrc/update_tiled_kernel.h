@@ -26,11 +26,11 @@
 // p - 1, p, p + 1 are accumulated in three rolling register sets.
 //
 // What bounds it.  With FP32 storage, memory: on the 512 x 256 x 256 channel
-// a kernel with the same loads and stores and no arithmetic takes 545 us
-// (its ten streams in and ten out reach 4.9 TB/s where one plain copy reaches
-// 6.0); the arithmetic alone takes 263 us.  With 16-bit storage the two are
-// near each other (326 and 275 us).  So the plane loop is built to overlap
-// them:
+// its counted HBM traffic (1.15 x its algorithmic bytes) moves at 97 % of the
+// rate of a plain copy (ten streams in and ten out without arithmetic, in an
+// older loop, took 545 us); the arithmetic alone takes 263 us.  With 16-bit
+// storage the two are near each other (326 and 275 us).  So the plane loop is
+// built to overlap them:
 //  - Interior and halo waves run loops of their own (wave-uniform branch), so
 //    every wait for memory counts exactly what is in flight.  In one shared
 //    loop the waits at the merge points covered loads issued a moment before
@@ -42,7 +42,7 @@
 //    to, exchange and sum one of the three cz slices only (64^3 periodic 10.9
 //    -> 10.1 us).
 // 512 x 256 x 256 channel FP32 559 -> 533 us, FP16 430 -> 392 us; 64^3
-// periodic FP32 11.8 -> 10.1 us.
+// periodic FP32 11.8 -> 10.1 us (all in tiles of 12 rows).
 // Tried without gain: two columns of two fields per lane and memory
 // instruction for 16-bit storage (sorting them costs what the fewer
 // instructions save), two resident blocks of 6 or 7 rows per CU (FP16 485 us
@@ -629,12 +629,13 @@ bool streams_out(const StepParams& p) {
 // blocks of an XCD push the halves of stored lines out of its L2 before the
 // neighbour completes them, so the loads run ahead less: FP32 on every such
 // grid (us, two planes ahead / late: 333 x 101 x 77 45.0 / 44.5, 181 x 428 x
-// 145 220 / 212), 16-bit storage in tiles of 12 rows without
-// a force field where two levels stay about in the Infinity Cache (us, late /
-// a plane ahead: 110 x 131 x 313 FP16 61.4 / 64.8, 271 x 271 x 39 44.1 / 46.5,
-// 160 x 200 x 210, 269 MB, 86.5 / 89.2, 77 x 300 x 300, 277 MB, 124.3 / 126.3;
-// beyond, 129 x 400 x 140, 289 MB, 124.7 / 121.1, 250^3 203.5 / 196.1; with a
-// field 160 x 992 x 32 70.9 / 66.5; 13 rows 333 x 210 x 140 143.6 / 137).
+// 145 220 / 212); 16-bit D3Q27 in tiles of 12 rows, without walls or a force
+// field, where two levels stay about in the Infinity Cache (us, a plane ahead /
+// late: 110 x 131 x 313 FP16 64.8 / 61.4, 271 x 271 x 39 46.5 / 44.1, 160 x 200
+// x 210, 269 MB, 89.2 / 86.5, 77 x 300 x 300, 277 MB, 126.3 / 124.3; beyond, 129
+// x 400 x 140, 289 MB, 121.1 / 124.7, 250^3 196.1 / 203.5; with a field 160 x
+// 992 x 32 66.5 / 70.9; 13 rows 333 x 210 x 140 137 / 143.6; walls and D3Q19
+// gain 2 to 5 % from it, but are faster than before without).
 template <class S>
 bool loads_late(const StepParams& p) {
     return !rows_whole_lines<S>(p) && 40 * (size_t)p.geo.N <= kInfinityCacheBytes / 20 * 21;
@@ -650,7 +651,7 @@ hipError_t launch_t(const void* in, void* out, const StepParams& p, hipStream_t 
             return launch_k<S, false, false, ORDER, LAT, true, true>(in, out, p, s);
         }
     if (nt) return launch_k<S, WALLS, FIELD, ORDER, LAT, true, false>(in, out, p, s);
-    if constexpr (sizeof(typename S::T) == 2 && TY == kFrameY && !FIELD)
+    if constexpr (sizeof(typename S::T) == 2 && TY == kFrameY && !FIELD && !WALLS && LAT == 27)
         if (loads_late<S>(p)) return launch_k<S, WALLS, FIELD, ORDER, LAT, false, false, true>(in, out, p, s);
     return launch_k<S, WALLS, FIELD, ORDER, LAT, false, false>(in, out, p, s);
 }
